@@ -425,9 +425,12 @@ lbl_status lbl_abstraction_info(lbl_abs_t a, lbl_abs_info *out)
     if (a->sp) {
         const SparseLayout &sp = *a->sp;
         const SpTiling &t = sp.tilings[0];
-        const uint64_t entry_bytes = sp.nnz * (sizeof(uint16_t) + sizeof(uint64_t));
+        const uint64_t word_bytes = sp.nnz * (sizeof(uint16_t) + sizeof(uint64_t));
+        const uint64_t run_bytes = sp.n_ent * sizeof(uint64_t);
+        // what the tile kernels read: run entries, or the words themselves
+        const uint64_t entry_bytes = sp.ent ? run_bytes : word_bytes;
         out->sparse_entries = sp.nnz;
-        out->sparse_bytes = entry_bytes + sp.round_bytes;
+        out->sparse_bytes = word_bytes + run_bytes + sp.round_bytes;
         // the one-frame label kernel's reads of the layout: entries, its
         // tasks and rounds, and the local rows of its compact partial slots
         out->sparse_frame_bytes = entry_bytes + (uint64_t)t.n_tiles * kTileWaves * sizeof(SpTask) +
@@ -443,7 +446,7 @@ lbl_status lbl_abstraction_info(lbl_abs_t a, lbl_abs_info *out)
         const DirectLayout &d = sp.direct;
         if (d.chunks) {
             out->sparse_tiles_direct = d.n_tiles;
-            out->sparse_frame_bytes_direct = entry_bytes + d.n_chunks * sizeof(SpChunk) +
+            out->sparse_frame_bytes_direct = word_bytes + d.n_chunks * sizeof(SpChunk) +
                                              d.n_parts * sizeof(DirectPart) + (d.n_tiles + 1ull) * sizeof(uint32_t);
         }
     }

@@ -35,7 +35,8 @@ struct GroupDesc {
     const uint32_t *word_cell;
     uint64_t *Ow;             // bitpacked plans: [n_words][G64][64] masks, one per column
                               // (64 cells each); sparse plans: [n_words][G64][256] nibble
-                              // tables
+                              // tables, or [n_words][G64][64] masks, one per cell, for
+                              // layouts in run entries
     const LaneDesc *lanes;    // [G64][64]
     const SegDesc *segs;      // the jobs of lane group gi: segs[lg_seg[gi] .. lg_seg[gi + 1])
     const uint32_t *lg_seg;   // [G64 + 1]
@@ -50,6 +51,7 @@ struct GroupDesc {
     const uint32_t *sp_rb_tile;  // [n_rb + 1] first tile of each row block
     const uint16_t *sp_row;
     const uint64_t *sp_val;
+    const uint64_t *sp_ent;      // run entries (null: the layout is in nibble entries)
     uint64_t max_entry;
     uint64_t *P;                 // [G64][n_slots] compact, else [G64][n_tiles][kRowBlock] (null when fused)
     // compact partials (the tiling's slot lists; null: full partials): tile

@@ -232,6 +232,7 @@ lbl_status plan_batch(const JobRef *jobs, size_t n_jobs, int device, BatchPlan *
                 g.n_rb = a->sp->n_rb;
                 g.sp_row = a->sp->row;
                 g.sp_val = a->sp->val;
+                g.sp_ent = a->sp->ent;
                 g.max_entry = std::max<uint64_t>(a->sp->nnz, 1) - 1;
             }
             p.lane_off.push_back(p.lanes.size());

@@ -5,6 +5,7 @@
 #include <vector>
 
 #include "lbl_internal.h"
+#include "runs.h"
 
 namespace lbl {
 
@@ -37,6 +38,13 @@ constexpr size_t kTileLds = ((size_t)kRowBlock + (size_t)kTileWaves * kRing * kT
 // The same with 32-bit masks (frames of at most 32 propositions): 66 KiB, so
 // two tile workgroups share a CU.
 constexpr size_t kTileLds32 = ((size_t)kRowBlock + (size_t)kTileWaves * kRing * kTabWords) * sizeof(uint32_t);
+// The same for the run tables of a layout in run entries (138 KiB and 69 KiB:
+// one and two workgroups per CU).
+constexpr size_t kRunLds = ((size_t)kRowBlock + (size_t)kTileWaves * 2 * kRunWords) * sizeof(uint64_t);
+constexpr size_t kRunLds32 = ((size_t)kRowBlock + (size_t)kTileWaves * 2 * kRunWords) * sizeof(uint32_t);
+static_assert(kRowBlock == 1u << (63 - kRunRowBit), "a run entry's local row");
+// Rounds a wavefront of the run kernels has in flight.
+constexpr int kRunStages = 2;
 
 // One wavefront's share of a tile: consecutive entries lo .. of one row
 // block, processed as rounds [round0, round0 + n_rounds).
@@ -140,6 +148,11 @@ struct SparseLayout {
     uint64_t n_segments = 0;     // non-empty (row block, word) segments
     uint16_t *row = nullptr;     // device [nnz] row within the row block
     uint64_t *val = nullptr;     // device [nnz] word value
+    // Run entries (runs.h): the same segments, their words as run codes, and
+    // the tilings below over them.  Null when the nibble kernels label the
+    // layout (see use_runs).
+    uint64_t n_ent = 0;
+    uint64_t *ent = nullptr;     // device [n_ent]
     uint32_t n_used = 0;         // words held by some entry (their tables are packed per frame)
     uint32_t *used_words = nullptr;  // device [n_used] ascending, or null when every word is used
     uint32_t *pack_first = nullptr;  // device [n_used] the first cell id of each packed word
@@ -217,6 +230,15 @@ struct TilingHost {
 };
 void make_tiling(const std::vector<uint64_t> &seg_start, const std::vector<uint32_t> &seg_word,
                  const std::vector<uint64_t> &rb_seg, const std::vector<uint32_t> &tiles_rb, TilingHost *out);
+// The same for run entries: start[s] .. start[s + 1] are those of segment s.
+// A round is up to 64 consecutive entries from any offset (lane_lo is 0) and
+// builds at most one segment's run tables.
+void make_run_tiling(const std::vector<uint64_t> &start, const std::vector<uint32_t> &seg_word,
+                     const std::vector<uint64_t> &rb_seg, const std::vector<uint32_t> &tiles_rb, TilingHost *out);
+std::vector<double> run_costs(const std::vector<uint64_t> &start, const std::vector<uint64_t> &rb_seg);
+// Whether a layout of nnz words that take n_ent run entries is labeled by the
+// run kernels.
+bool use_runs(uint64_t nnz, uint64_t n_ent);
 // Compact partial slots of a tiling (host): row[e] is the local row of entry
 // e; tile i of block rb covers entries [tasks[i * kTileWaves].lo, the next
 // tile's first entry or the block's end).  Fails (false) if the slots

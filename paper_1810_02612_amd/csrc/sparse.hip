@@ -35,6 +35,9 @@
 //                  labels.
 //   k_combine      OR of a row's partials over the tiles of its row block ->
 //                  the caller's L bytes (0/1).
+// Layouts in run entries (runs.h; use_runs) are labeled by the same three
+// steps with k_pack_cells, which writes the cells' masks, and k_label_runs,
+// whose wavefronts build the tables of 8-cell rows themselves.
 // Frames of at most 4 propositions take two other kernels instead:
 //   k_pack_masks   O -> NP proposition masks per used word (bit b = cell b);
 //                  the grid also zeroes L.
@@ -50,6 +53,7 @@
 
 #include "batch.h"
 #include "profile.h"
+#include "runs.h"
 #include "sparse.h"
 #include "tables.h"
 
@@ -156,6 +160,53 @@ k_seg_fill(const uint64_t *__restrict__ wm_ptr, const uint32_t *__restrict__ wm_
     }
 }
 
+// Segments of the run layout, one wavefront each: the number of run entries
+// of segment s (entries seg[s] .. seg[s + 1] of sp_val).
+__global__ void __launch_bounds__(256)
+k_run_count(const uint64_t *__restrict__ seg, uint64_t n_seg, const uint64_t *__restrict__ sp_val,
+            uint32_t *__restrict__ cnt)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t s = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (s >= n_seg) return;
+    uint32_t n = 0;
+    for (uint64_t e = seg[s] + lane; e < seg[s + 1]; e += 64) n += word_entries(sp_val[e]);
+    for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off);
+    if (lane == 0) cnt[s] = n;
+}
+
+// The run entries of every segment, from run_seg[s], in the order of its
+// words (a word's pieces follow each other), and their local rows.
+__global__ void __launch_bounds__(256)
+k_run_fill(const uint64_t *__restrict__ seg, const uint64_t *__restrict__ run_seg, uint64_t n_seg,
+           const uint16_t *__restrict__ sp_row, const uint64_t *__restrict__ sp_val, uint64_t *__restrict__ ent,
+           uint16_t *__restrict__ ent_row)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t s = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (s >= n_seg) return;
+    uint64_t at = run_seg[s];
+    const uint64_t end = run_seg[s + 1];
+    for (uint64_t e0 = seg[s]; e0 < seg[s + 1]; e0 += 64) {
+        const uint64_t e = e0 + lane;
+        const bool in = e < seg[s + 1];
+        const uint64_t v = in ? sp_val[e] : 0ull;
+        const uint32_t n = in ? word_entries(v) : 0u;
+        uint32_t upto = n;  // inclusive sum over the lanes
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = __shfl_up(upto, off);
+            if (lane >= (uint32_t)off) upto += o;
+        }
+        const uint64_t dst = at + upto - n;
+        for (uint32_t j = 0; j < n; ++j)
+            if (dst + j < end) {
+                ent[dst + j] = word_codes(v, j) | (uint64_t)sp_row[e] << kRunRowBit | (s & 1ull) << 63;
+                ent_row[dst + j] = sp_row[e];
+            }
+        at += __shfl(upto, 63);
+    }
+}
+
 // ---------------------------------------------------------------- per frame
 
 // Native vector types: loads and stores of these through address-space
@@ -180,6 +231,21 @@ __device__ __forceinline__ uint64_t word_lane_cell(const uint32_t *__restrict__ 
     return (uint64_t)first[i] + (morton ? (uint64_t)lane : (uint64_t)dy * nx + dx);
 }
 
+// z-order index of cell (x, y) of a word's 8 x 8 block.
+__device__ __forceinline__ uint32_t word_z(uint32_t x, uint32_t y)
+{
+    return (y & 1u) | ((x & 1u) << 1) | ((y & 2u) << 1) | ((x & 2u) << 2) | ((y & 4u) << 2) | ((x & 4u) << 3);
+}
+
+// word_lane_cell with the word's cells row by row: lane 8y + x holds cell
+// (x, y), as the run tables are built.
+__device__ __forceinline__ uint64_t word_lane_cell_rows(const uint32_t *__restrict__ first, uint32_t i, uint32_t lane,
+                                                        uint32_t nx, uint32_t morton)
+{
+    const uint32_t x = lane & 7u, y = lane >> 3;
+    return (uint64_t)first[i] + (morton ? (uint64_t)word_z(x, y) : (uint64_t)y * nx + x);
+}
+
 // Lane b's mask of the propositions cell b of packed word i meets (cell b as
 // word_lane_cell places it).  When n_props is 16, 32 or 64 and O is 16-byte
 // aligned, the wavefront reads the word's frame bytes in 16-byte units taken
@@ -188,12 +254,15 @@ __device__ __forceinline__ uint64_t word_lane_cell(const uint32_t *__restrict__ 
 // lines instead of a 16-byte piece of 64 different cells; each unit's 16 bits
 // go to their cell's place in the wavefront's 512-byte stage, from which lane
 // b then reads cell b.  Otherwise every lane reads its own cell's bytes.
+// ROWS: lane 8y + x holds cell (x, y) instead (word_lane_cell_rows).
+template <bool ROWS>
 __device__ __forceinline__ uint64_t word_cell_mask(const uint8_t *__restrict__ O, uint32_t n_props,
                                                    const uint32_t *__restrict__ first, uint32_t i, uint32_t lane,
                                                    uint32_t nx, uint32_t morton, uint64_t *stage)
 {
     if (!((n_props == 16 || n_props == 32 || n_props == 64) && (reinterpret_cast<uintptr_t>(O) & 15u) == 0))
-        return byte_mask(O + word_lane_cell(first, i, lane, nx, morton) * n_props, n_props);
+        return byte_mask(O + (ROWS ? word_lane_cell_rows(first, i, lane, nx, morton)
+                                   : word_lane_cell(first, i, lane, nx, morton)) * n_props, n_props);
     const uint32_t sh = n_props == 16 ? 0u : n_props == 32 ? 1u : 2u;  // log2 of a cell's units
     const uint32_t last = (1u << sh) - 1u;                               // loads per lane - 1
     const uint64_t c0 = first[i];
@@ -207,9 +276,13 @@ __device__ __forceinline__ uint64_t word_cell_mask(const uint8_t *__restrict__ O
         const uint32_t x = k & 7u, y = k >> 3;          // the cell's place in the word's 8 x 8 block
         const uint64_t cell = c0 + (morton ? (uint64_t)k : (uint64_t)y * nx + x);
         q[j] = *reinterpret_cast<const uint4 *>(O + cell * n_props + 16u * part);
-        const uint32_t b = morton ? k
-                                  : (y & 1u) | ((x & 1u) << 1) | ((y & 2u) << 1) | ((x & 2u) << 2) | ((y & 4u) << 2) |
-                                        ((x & 4u) << 3);
+        uint32_t b;  // the lane that holds the cell
+        if constexpr (ROWS)
+            b = morton ? ((k >> 1) & 1u) | ((k >> 2) & 2u) | ((k >> 3) & 4u) |
+                             ((k & 1u) | ((k >> 1) & 2u) | ((k >> 2) & 4u)) << 3
+                       : k;
+        else
+            b = morton ? k : word_z(x, y);
         at[j] = 4u * b + part;  // 16-bit slot of the unit's bits in the stage
     }
     // LDS accesses of one wavefront complete in issue order: the zeroing
@@ -238,13 +311,29 @@ k_pack_tables(const uint8_t *__restrict__ O, uint32_t n_props, const uint32_t *_
     const uint32_t i = blockIdx.x * 4 + wave;
     if (i >= n_items) return;  // whole wavefronts
     const uint32_t w = words ? words[i] : i;
-    const uint64_t mask = word_cell_mask(O, n_props, first, i, lane, nx, morton, stage[wave]);
+    const uint64_t mask = word_cell_mask<false>(O, n_props, first, i, lane, nx, morton, stage[wave]);
     if constexpr (sizeof(M) == 8)
         write_tables(mask, Tg + (uint64_t)w * 256, lane);
     else
         write_tables32((uint32_t)mask, Tg + (uint64_t)w * 256, lane);
 }
 
+// As k_pack_tables for a layout in run entries: the word's cell masks, lane
+// 8y + x's at Tm[w * 64 + 8y + x].  The tile kernel builds the word's run
+// tables from them.
+template <typename M>
+__global__ void __launch_bounds__(256)
+k_pack_cells(const uint8_t *__restrict__ O, uint32_t n_props, const uint32_t *__restrict__ first, uint32_t nx,
+             uint32_t morton, const uint32_t *__restrict__ words, uint32_t n_items, M *__restrict__ Tm)
+{
+    __shared__ uint64_t stage[4][64];
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t i = blockIdx.x * 4 + wave;
+    if (i >= n_items) return;  // whole wavefronts
+    const uint32_t w = words ? words[i] : i;
+    Tm[(uint64_t)w * 64 + lane] = (M)word_cell_mask<true>(O, n_props, first, i, lane, nx, morton, stage[wave]);
+}
 
 // Frames of at most NP <= 4 propositions: one wavefront per word, lane b
 // holding cell b of packed word i as in k_pack_tables; the word's NP proposition masks
@@ -311,6 +400,16 @@ __device__ __forceinline__ uint32_t select_by_lane(uint64_t mask, uint32_t a, ui
 {
     uint32_t r;
     asm("v_cndmask_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(mask));
+    return r;
+}
+
+// base + (x << S) in one instruction (as plain code, with a bit field extract
+// before it, the compiler takes three: shift, mask and add).
+template <int S>
+__device__ __forceinline__ uint32_t lshl_add(uint32_t x, uint32_t base)
+{
+    uint32_t r;
+    asm("v_lshl_add_u32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "n"(S), "v"(base));
     return r;
 }
 
@@ -543,6 +642,124 @@ __device__ __forceinline__ void tile_accumulate(const SpTask *__restrict__ wg_ta
     __syncthreads();
 }
 
+// tile_accumulate for a layout in run entries: Tm + w * tm_stride holds the
+// 64 cell masks of word w.  A round takes the first n of 64 entries from its
+// own offset (n in the record's lane_hi; no lane is skipped at the front), in
+// at most two segments, and builds at most one segment's run tables.  Each
+// entry says itself which of the wavefront's two table slots it reads.
+//
+// Bound by the LDS: at 200k x 512^2 x 64 it is busy 35k of the 52k cycles a
+// CU runs (half of that for the table builds, eight 8-byte stores per lane
+// for each of 103k segments), the vector units 27k; loading the entries
+// alone, without lookups, takes 17 us of the 26, launch and write-back 6.
+// There: 45 vector and 14 LDS instructions per 64 entries where the nibble
+// kernel needs 51 and 19, 26.0 us against 28.6 (rocprofv3 medians), entries
+// 80 MB against 99; packing 5.2 us against 7.1, as it writes 512 bytes per
+// word and not 2 KiB of tables.  50k x 256^2 x 32: 7.0 us and 3.0 against 7.7
+// and 4.2.  Three and four rounds in flight: 26.2 and 27.5 us.
+template <int WAVES, typename M>
+__device__ __forceinline__ void run_accumulate(const SpTask *__restrict__ wg_tasks,
+                                               const SpRound *__restrict__ rounds,
+                                               const uint64_t *__restrict__ ent, const M *__restrict__ Tm,
+                                               uint64_t tm_stride, void *lds)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    M *acc = static_cast<M *>(lds);
+    M *tab = acc + kRowBlock + wave * (2 * kRunWords);
+    typedef __attribute__((address_space(1))) const uint32_t gu32;
+    typedef __attribute__((address_space(3))) const M lm;
+    const gu32 *task = (const gu32 *)(wg_tasks + wave);
+    const uint64_t tk_lo = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)task[0]) |
+                           ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)task[1]) << 32);
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)task[2]);
+    const uint32_t round0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)task[3]);
+    struct Stage {
+        uint32_t rec;   // lanes 0-3: the record of the stage's next round
+        uint32_t meta;
+        uint64_t x;     // this lane's entry
+        M m;            // its cell of the word whose tables the round builds
+    };
+    // the loads as in tile_accumulate: unconditional, through raw buffer
+    // resources, the entries and masks of a round kRunStages - 1 rounds ahead
+    // and its record kRunStages rounds before that
+    const __amdgpu_buffer_rsrc_t r_rec = uniform_rsrc(rounds + round0);
+    const __amdgpu_buffer_rsrc_t r_ent = uniform_rsrc(ent + tk_lo);
+    const uint32_t o_rec = (lane & 3u) * 4u, o_ent = lane * 8u, o_m = lane * (uint32_t)sizeof(M);
+    auto load_rec = [&](uint32_t i) {
+        return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r_rec, (int)o_rec, (int)(min(i, n - 1) * 16u), 0);
+    };
+    auto fetch = [&](Stage &st, uint32_t i) {
+        const uint32_t e_off = (uint32_t)__builtin_amdgcn_readlane((int)st.rec, 0);
+        const uint32_t tword = (uint32_t)__builtin_amdgcn_readlane((int)st.rec, 1);
+        st.meta = (uint32_t)__builtin_amdgcn_readlane((int)st.rec, 3);
+        st.rec = load_rec(i + kRunStages);
+        st.x = __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(r_ent, (int)o_ent, (int)(e_off * 8u), 0));
+        // a round that builds no tables loads one line of its last word
+        const __amdgpu_buffer_rsrc_t r_m = uniform_rsrc(Tm + (uint64_t)tword * tm_stride);
+        const uint32_t ml = (st.meta & (kMetaBuild0 | kMetaBuild1)) ? o_m : 0u;
+        if constexpr (sizeof(M) == 8)
+            st.m = __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(r_m, (int)ml, 0, 0));
+        else
+            st.m = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r_m, (int)ml, 0, 0);
+    };
+    uint32_t slot_a, slot_b;
+    asm("v_mov_b32 %0, %1" : "=v"(slot_a) : "s"(lds_addr(tab)));
+    asm("v_mov_b32 %0, %1" : "=v"(slot_b) : "s"(lds_addr(tab) + kRunWords * (uint32_t)sizeof(M)));
+    auto process = [&](const Stage &st) {
+        const uint32_t meta = st.meta;
+        if (meta & (kMetaBuild0 | kMetaBuild1)) {
+            const uint32_t s = ((meta & kMetaSlot0) ? 1u : 0u) ^ ((meta & kMetaBuild1) ? 1u : 0u);
+            build_runs<M>(st.m, tab + s * kRunWords, lane);
+        }
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t lo = (uint32_t)st.x, hi = (uint32_t)(st.x >> 32);
+        const uint32_t t = (int32_t)hi < 0 ? slot_b : slot_a;
+        constexpr uint32_t sz = sizeof(M);
+        M q[8];
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) {
+            const uint32_t c = __builtin_amdgcn_ubfe(k < 5 ? lo : hi, run_code_bit(k) & 31u, 6u);
+            q[k] = *reinterpret_cast<lm *>(static_cast<uintptr_t>(lshl_add<sz == 8 ? 3 : 2>(c, t) + k * (kRunRow * sz)));
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);  // the eight LDS reads first
+        M a = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) a |= q[k];
+        // lanes past the round's entries hold another round's; zero results
+        // are skipped (an OR of zero still costs LDS time)
+        if (lane < ((meta >> 8) & 0xFFu) && a)
+            __hip_atomic_fetch_or(acc + __builtin_amdgcn_ubfe(hi, kRunRowBit - 32, 13u), a, __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+        __builtin_amdgcn_wave_barrier();  // later builds overwrite these tables
+        // counts as used also when no tables were built (see tile_accumulate)
+        if constexpr (sizeof(M) == 8)
+            asm volatile("" ::"v"((uint32_t)st.m), "v"((uint32_t)(st.m >> 32)));
+        else
+            asm volatile("" ::"v"(st.m));
+    };
+    Stage st[kRunStages];
+    if (n > 0) {
+#pragma unroll
+        for (int k = 0; k < kRunStages; ++k) st[k].rec = load_rec(k);
+#pragma unroll
+        for (int k = 0; k + 1 < kRunStages; ++k) fetch(st[k], k);
+    }
+    for (uint32_t i = threadIdx.x; i < kRowBlock * sizeof(M) / 16; i += 64 * WAVES)
+        reinterpret_cast<v4u32 *>(acc)[i] = v4u32{0u, 0u, 0u, 0u};
+    if (lane < 16) tab[(lane >> 3) * kRunWords + (lane & 7u) * kRunRow] = 0;  // the entries of rows without cells
+    __syncthreads();
+    // as in tile_accumulate, the last round may be processed again
+    for (uint32_t i = 0; i < n; i += kRunStages) {
+#pragma unroll
+        for (int k = 0; k < kRunStages; ++k) {
+            fetch(st[(k + kRunStages - 1) % kRunStages], i + k + kRunStages - 1);
+            process(st[k]);
+        }
+    }
+    __syncthreads();
+}
+
 // The tile's accumulators as its partials: every row of the block at
 // Pt[0 .. kRowBlock), or (compact) only the n_slot rows slot_row[..] it
 // touches at Pt[0 .. n_slot).  Streaming stores: the partials are read once,
@@ -585,6 +802,24 @@ k_label_tiles(const uint32_t *__restrict__ block_tile, const SpTask *__restrict_
     extern __shared__ uint64_t lds[];
     const uint32_t tile = block_tile[blockIdx.x];
     tile_accumulate<WAVES, M>(tasks_launch + (uint64_t)blockIdx.x * WAVES, rounds, sp_row, sp_val, Tg, 256, lds);
+    if (tile_slot) {
+        const uint32_t s0 = tile_slot[tile], s1 = tile_slot[tile + 1];
+        write_partials_compact<WAVES, M>(lds, P + s0, slot_row + s0, s1 - s0);
+    } else {
+        write_partials<WAVES, M>(lds, P + (uint64_t)tile * kRowBlock);
+    }
+}
+
+// k_label_tiles for a layout in run entries (Tm: k_pack_cells' masks).
+template <int WAVES, typename M>
+__global__ void __launch_bounds__(64 * WAVES, sizeof(M) == 8 ? 1 : 2)
+k_label_runs(const uint32_t *__restrict__ block_tile, const SpTask *__restrict__ tasks_launch,
+             const SpRound *__restrict__ rounds, const uint64_t *__restrict__ ent, const M *__restrict__ Tm,
+             M *__restrict__ P, const uint32_t *__restrict__ tile_slot, const uint16_t *__restrict__ slot_row)
+{
+    extern __shared__ uint64_t lds[];
+    const uint32_t tile = block_tile[blockIdx.x];
+    run_accumulate<WAVES, M>(tasks_launch + (uint64_t)blockIdx.x * WAVES, rounds, ent, Tm, 64, lds);
     if (tile_slot) {
         const uint32_t s0 = tile_slot[tile], s1 = tile_slot[tile + 1];
         write_partials_compact<WAVES, M>(lds, P + s0, slot_row + s0, s1 - s0);
@@ -845,7 +1080,8 @@ __device__ __forceinline__ void emit_tile(uint64_t *lds, const GroupDesc &g, uin
 }
 
 // One tile item of a batch: pass it.group, tile it.tile, lane group it.gi.
-// The pass's nibble tables are [w][G64][256].  Passes on a tiling with one
+// The pass's nibble tables are [w][G64][256] (cell masks [w][G64][64] for a
+// layout in run entries).  Passes on a tiling with one
 // tile per row block (fused) write the label bytes themselves; the others
 // write partials for k_combine_batch: compact ([G64][n_slots], the rows each
 // tile touches) when the tiling has slot lists, else [G64][n_tiles][kRowBlock].
@@ -853,8 +1089,12 @@ template <int WAVES>
 __device__ __forceinline__ void batch_tile(const GroupDesc *__restrict__ groups, const TileItem &it, uint64_t *lds)
 {
     const GroupDesc &g = groups[it.group];
-    tile_accumulate<WAVES, uint64_t>(g.sp_tasks + (uint64_t)it.tile * WAVES, g.sp_rounds, g.sp_row, g.sp_val,
-                                     g.Ow + (uint64_t)it.gi * 256, (uint64_t)g.G64 * 256, lds);
+    if (g.sp_ent)
+        run_accumulate<WAVES, uint64_t>(g.sp_tasks + (uint64_t)it.tile * WAVES, g.sp_rounds, g.sp_ent,
+                                        g.Ow + (uint64_t)it.gi * 64, (uint64_t)g.G64 * 64, lds);
+    else
+        tile_accumulate<WAVES, uint64_t>(g.sp_tasks + (uint64_t)it.tile * WAVES, g.sp_rounds, g.sp_row, g.sp_val,
+                                         g.Ow + (uint64_t)it.gi * 256, (uint64_t)g.G64 * 256, lds);
     if (g.fused) {
         emit_tile<WAVES>(lds, g, it.gi, it.tile);
     } else if (g.tile_slot) {
@@ -973,10 +1213,12 @@ k_pack_batch_tables(const GroupDesc *__restrict__ groups, const PackItem *__rest
     const bool zo = g.morton != 0;
     // lane b is the cell at (dx, dy) of the word's 8 x 8 tile, x taking the
     // odd bits of b; in z-order ids it is the word's cell b
-    const uint32_t dx = ((lane >> 1) & 1u) | ((lane >> 2) & 2u) | ((lane >> 3) & 4u);
-    const uint32_t dy = (lane & 1u) | ((lane >> 1) & 2u) | ((lane >> 2) & 4u);
+    // (for a layout in run entries, lane 8y + x is the cell at (x, y))
+    const bool rows = g.sp_ent != nullptr;
+    const uint32_t dx = rows ? lane & 7u : ((lane >> 1) & 1u) | ((lane >> 2) & 2u) | ((lane >> 3) & 4u);
+    const uint32_t dy = rows ? lane >> 3 : (lane & 1u) | ((lane >> 1) & 2u) | ((lane >> 2) & 4u);
     const uint32_t n_run = zo ? 1u : 8u, run_cells = zo ? 64u : 8u;
-    const uint32_t my_run = zo ? 0u : dy, my_pos = zo ? lane : dx;
+    const uint32_t my_run = zo ? 0u : dy, my_pos = zo ? (rows ? word_z(dx, dy) : lane) : dx;
     const global_u32 *word_cell = (const global_u32 *)g.word_cell;
     for (uint32_t w = it.w0; w < it.w1; ++w) {
         // the word's first cell (dx = dy = 0), wavefront-uniform (read into
@@ -1026,7 +1268,10 @@ k_pack_batch_tables(const GroupDesc *__restrict__ groups, const PackItem *__rest
             m |= byte_mask_words(stage + (off >> 2), off & 3u, np) << bit;
             __builtin_amdgcn_wave_barrier();  // the next job overwrites the stage
         }
-        write_tables(m, g.Ow + ((uint64_t)w * g.G64 + it.gi) * 256, lane);
+        if (rows)
+            g.Ow[((uint64_t)w * g.G64 + it.gi) * 64 + lane] = m;
+        else
+            write_tables(m, g.Ow + ((uint64_t)w * g.G64 + it.gi) * 256, lane);
     }
 }
 
@@ -1218,6 +1463,35 @@ std::vector<double> chunk_costs(const std::vector<uint64_t> &seg_start, const st
     return c;
 }
 
+// Fill block_tile: tiles ranked by the word at their middle entry, the ranks
+// split into kXcds consecutive groups, group g taking blocks g, g + kXcds, ...
+void order_tiles(const std::vector<uint64_t> &seg_start, const std::vector<uint32_t> &seg_word, TilingHost *out)
+{
+    const uint32_t n_tiles = (uint32_t)(out->tasks.size() / kTileWaves);
+    std::vector<std::pair<uint32_t, uint32_t>> key(n_tiles);
+    for (uint32_t i = 0; i < n_tiles; ++i) {
+        const SpTask &f = out->tasks[(size_t)i * kTileWaves];
+        const SpTask &l = out->tasks[(size_t)i * kTileWaves + kTileWaves - 1];
+        uint64_t hi = l.lo;  // end of the tile's entries: its last task's end
+        for (uint32_t r = 0; r < l.n_rounds; ++r) {
+            const SpRound &x = out->rounds[l.round0 + r];
+            hi = std::max<uint64_t>(hi, l.lo + x.e_off + ((x.meta >> 8) & 0xFFu));
+        }
+        const uint64_t mid = (f.lo + hi) / 2;
+        uint32_t w = 0;
+        if (hi > f.lo) {
+            const uint64_t sidx = std::upper_bound(seg_start.begin(), seg_start.end(), mid) - seg_start.begin() - 1;
+            w = seg_word[std::min<uint64_t>(sidx, seg_word.size() - 1)];
+        }
+        key[i] = {w, i};
+    }
+    std::stable_sort(key.begin(), key.end());
+    out->block_tile.assign(n_tiles, 0);
+    uint32_t rank = 0;
+    for (uint32_t g = 0; g < kXcds; ++g)
+        for (uint32_t b = g; b < n_tiles; b += kXcds) out->block_tile[b] = key[rank++].second;
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------- host: tilings
@@ -1341,31 +1615,109 @@ void make_tiling(const std::vector<uint64_t> &seg_start, const std::vector<uint3
             out->tasks.push_back(t);
         }
     }
-    // launch order: tiles ranked by the word at their middle entry, the ranks
-    // split into kXcds consecutive groups, group g taking blocks g, g + kXcds, ...
-    const uint32_t n_tiles = (uint32_t)(out->tasks.size() / kTileWaves);
-    std::vector<std::pair<uint32_t, uint32_t>> key(n_tiles);
-    for (uint32_t i = 0; i < n_tiles; ++i) {
-        const SpTask &f = out->tasks[(size_t)i * kTileWaves];
-        const SpTask &l = out->tasks[(size_t)i * kTileWaves + kTileWaves - 1];
-        uint64_t hi = l.lo;  // end of the tile's entries: its last task's end
-        for (uint32_t r = 0; r < l.n_rounds; ++r) {
-            const SpRound &x = out->rounds[l.round0 + r];
-            hi = std::max<uint64_t>(hi, l.lo + x.e_off + ((x.meta >> 8) & 0xFFu));
+    order_tiles(seg_start, seg_word, out);
+}
+
+namespace {
+
+// Cost of building a segment's run tables, in rounds.
+constexpr double kRunBuildCost = 0.5;
+
+// The rounds of run entries [lo, hi) of one row block as one wavefront walks
+// them with empty tables at the start: up to 64 consecutive entries, at most
+// two segments and one table build per round.  sp: a segment at or before
+// the one holding lo (advanced in place).  emit(e, n, cut, a, build): the
+// round's first entry and entry count, how many of them lie in its first
+// segment a (64 if all), and -1 / 0 / 1 for no build / a / a + 1.
+template <class Emit>
+void walk_runs(const std::vector<uint64_t> &start, uint64_t lo, uint64_t hi, uint64_t &sp, Emit emit)
+{
+    int64_t built = -1;
+    for (uint64_t e = lo; e < hi;) {
+        while (start[sp + 1] <= e) ++sp;
+        const uint64_t a = sp, end_a = std::min(start[a + 1], hi);
+        const bool new_a = (int64_t)a > built;
+        uint64_t end = std::min(e + 64, end_a);
+        uint32_t cut = 64;
+        int build = new_a ? 0 : -1;
+        if (end == end_a && end < std::min(e + 64, hi) && !new_a) {
+            // segment a ends inside the round, with its tables already there
+            cut = (uint32_t)(end_a - e);
+            end = std::min(std::min(e + 64, hi), start[a + 2]);
+            build = 1;
         }
-        const uint64_t mid = (f.lo + hi) / 2;
-        uint32_t w = 0;
-        if (hi > f.lo) {
-            const uint64_t sidx = std::upper_bound(seg_start.begin(), seg_start.end(), mid) - seg_start.begin() - 1;
-            w = seg_word[std::min<uint64_t>(sidx, seg_word.size() - 1)];
-        }
-        key[i] = {w, i};
+        emit(e, (uint32_t)(end - e), cut, a, build);
+        if (build >= 0) built = (int64_t)a + build;
+        e = end;
     }
-    std::stable_sort(key.begin(), key.end());
-    out->block_tile.assign(n_tiles, 0);
-    uint32_t rank = 0;
-    for (uint32_t g = 0; g < kXcds; ++g)
-        for (uint32_t b = g; b < n_tiles; b += kXcds) out->block_tile[b] = key[rank++].second;
+}
+
+}  // namespace
+
+std::vector<double> run_costs(const std::vector<uint64_t> &start, const std::vector<uint64_t> &rb_seg)
+{
+    std::vector<double> out(rb_seg.size() - 1, 0.0);
+    for (size_t rb = 0; rb + 1 < rb_seg.size(); ++rb) {
+        uint64_t sp = rb_seg[rb];
+        walk_runs(start, start[rb_seg[rb]], start[rb_seg[rb + 1]], sp,
+                  [&](uint64_t, uint32_t, uint32_t, uint64_t, int build) { out[rb] += 1.0 + (build >= 0 ? kRunBuildCost : 0.0); });
+    }
+    return out;
+}
+
+void make_run_tiling(const std::vector<uint64_t> &start, const std::vector<uint32_t> &seg_word,
+                     const std::vector<uint64_t> &rb_seg, const std::vector<uint32_t> &tiles_rb, TilingHost *out)
+{
+    const size_t n_rb = rb_seg.size() - 1;
+    out->tasks.clear();
+    out->rounds.clear();
+    out->rb_tile.assign(n_rb + 1, 0);
+    std::vector<std::pair<uint64_t, double>> walked;  // a round's first entry, the cost before it
+    for (size_t rb = 0; rb < n_rb; ++rb) {
+        out->rb_tile[rb + 1] = out->rb_tile[rb] + tiles_rb[rb];
+        const uint64_t E0 = start[rb_seg[rb]], E1 = start[rb_seg[rb + 1]];
+        const uint64_t m = (uint64_t)tiles_rb[rb] * kTileWaves;
+        // task boundaries at round starts of the block walked as one task, by
+        // the cost before them; task q's share is wave_share(q % kTileWaves)
+        walked.clear();
+        double C = 0;
+        uint64_t sp = rb_seg[rb];
+        walk_runs(start, E0, E1, sp, [&](uint64_t e, uint32_t, uint32_t, uint64_t, int build) {
+            walked.push_back({e, C});
+            C += 1.0 + (build >= 0 ? kRunBuildCost : 0.0);
+        });
+        double Wsum = 0;
+        for (uint64_t q = 0; q < m; ++q) Wsum += wave_share((uint32_t)(q % kTileWaves));
+        std::vector<uint64_t> bnd(m + 1, E1);
+        bnd[0] = E0;
+        {
+            size_t k = 0;
+            double wq = 0;
+            for (uint64_t q = 1; q < m; ++q) {
+                wq += wave_share((uint32_t)((q - 1) % kTileWaves));
+                const double want = C * wq / Wsum;
+                while (k < walked.size() && walked[k].second + 0.5 < want) ++k;
+                bnd[q] = k < walked.size() ? walked[k].first : E1;
+            }
+        }
+        sp = rb_seg[rb];
+        for (uint64_t q = 0; q < m; ++q) {
+            SpTask t{bnd[q], 0, (uint32_t)out->rounds.size()};
+            uint32_t tword = 0;  // word of the last tables built
+            walk_runs(start, bnd[q], bnd[q + 1], sp, [&](uint64_t e, uint32_t n, uint32_t cut, uint64_t a, int build) {
+                uint32_t meta = n << 8 | cut << 16;
+                if (build >= 0) {
+                    meta |= build == 0 ? kMetaBuild0 : kMetaBuild1;
+                    tword = seg_word[a + build];
+                }
+                if (a & 1) meta |= kMetaSlot0;  // slot of a segment = parity of its index
+                out->rounds.push_back(SpRound{(uint32_t)(e - t.lo), tword, 0, meta});
+                ++t.n_rounds;
+            });
+            out->tasks.push_back(t);
+        }
+    }
+    order_tiles(start, seg_word, out);
 }
 
 bool make_compact(const TilingHost &h, const std::vector<uint16_t> &row, const std::vector<uint64_t> &seg_start,
@@ -1472,6 +1824,7 @@ SparseLayout::~SparseLayout()
 {
     (void)hipFree(row);
     (void)hipFree(val);
+    (void)hipFree(ent);
     (void)hipFree(used_words);
     (void)hipFree(pack_first);
     for (SpTiling &t : tilings) {
@@ -1501,11 +1854,14 @@ hipError_t launch_pack_batch_tables(const GroupDesc *d_groups, const PackItem *d
     return hipGetLastError();
 }
 
+// a batch may mix layouts in run and in nibble entries
+constexpr size_t kBatchLds = kRunLds > kTileLds ? kRunLds : kTileLds;
+
 hipError_t launch_tiles_batch(const GroupDesc *d_groups, const TileItem *d_tiles, const uint32_t *d_launch,
                               uint32_t n_tiles, hipStream_t s)
 {
     if (n_tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_label_tiles_batch<kTileWaves>, dim3(n_tiles), dim3(64 * kTileWaves), kTileLds, s, d_groups,
+    hipLaunchKernelGGL(k_label_tiles_batch<kTileWaves>, dim3(n_tiles), dim3(64 * kTileWaves), kBatchLds, s, d_groups,
                        d_tiles, d_launch);
     return hipGetLastError();
 }
@@ -1514,7 +1870,7 @@ hipError_t launch_tiles_batch_queue(const GroupDesc *d_groups, const TileItem *d
                                     uint32_t *d_queues, uint32_t n_workgroups, hipStream_t s)
 {
     if (n_workgroups == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_label_tiles_queue<kTileWaves>, dim3(n_workgroups), dim3(64 * kTileWaves), kTileLds, s,
+    hipLaunchKernelGGL(k_label_tiles_queue<kTileWaves>, dim3(n_workgroups), dim3(64 * kTileWaves), kBatchLds, s,
                        d_groups, d_tiles, d_xcd_start, d_queues);
     return hipGetLastError();
 }
@@ -1661,6 +2017,52 @@ lbl_status sparse_part(const uint64_t *T, uint32_t row_stride, uint64_t n_rows, 
     return LBL_OK;
 }
 
+// Measured on 50k rows of 30 words of 64 random cells (label kernel, 64
+// propositions): at 1.15 run entries per word 11.1 us, nibble entries 11.1;
+// at 1.45, 12.1 against 11.6; at 2.0, 13.9 against 11.8.  Swept footprints
+// take 1.002 to 1.03.
+bool use_runs(uint64_t nnz, uint64_t n_ent) { return nnz != 0 && n_ent <= nnz + nnz / 4; }
+
+// The run entries of sp's words, when they label it (use_runs): sets sp->ent,
+// the first entry of every segment (start) and the entries' local rows.
+static lbl_status make_runs(SparseLayout *sp, const std::vector<uint64_t> &seg_start, std::vector<uint64_t> *start,
+                            std::vector<uint16_t> *rows)
+{
+    const uint64_t n_seg = sp->n_segments;
+    if (n_seg == 0 || n_seg >= (1ull << 32)) return LBL_OK;
+    const dim3 grid((unsigned)((n_seg + 3) / 4)), block(256);
+    uint64_t *d_seg = nullptr, *d_start = nullptr;
+    uint32_t *d_cnt = nullptr;
+    uint16_t *d_row = nullptr;
+    LBL_HIP_TRY(hipMalloc(&d_seg, (n_seg + 1) * sizeof(uint64_t)));
+    std::unique_ptr<uint64_t, decltype(&hipFree)> g_seg(d_seg, &hipFree);
+    LBL_HIP_TRY(hipMemcpy(d_seg, seg_start.data(), (n_seg + 1) * sizeof(uint64_t), hipMemcpyHostToDevice));
+    LBL_HIP_TRY(hipMalloc(&d_cnt, n_seg * sizeof(uint32_t)));
+    std::unique_ptr<uint32_t, decltype(&hipFree)> g_cnt(d_cnt, &hipFree);
+    hipLaunchKernelGGL(k_run_count, grid, block, 0, nullptr, d_seg, n_seg, sp->val, d_cnt);
+    LBL_HIP_TRY(hipGetLastError());
+    std::vector<uint32_t> cnt(n_seg);
+    LBL_HIP_TRY(hipMemcpy(cnt.data(), d_cnt, n_seg * sizeof(uint32_t), hipMemcpyDeviceToHost));
+    start->assign(n_seg + 1, 0);
+    for (uint64_t s = 0; s < n_seg; ++s) (*start)[s + 1] = (*start)[s] + cnt[s];
+    const uint64_t n = start->back();
+    if (!use_runs(sp->nnz, n)) return LBL_OK;
+    LBL_HIP_TRY(hipMalloc(&d_start, (n_seg + 1) * sizeof(uint64_t)));
+    std::unique_ptr<uint64_t, decltype(&hipFree)> g_start(d_start, &hipFree);
+    LBL_HIP_TRY(hipMemcpy(d_start, start->data(), (n_seg + 1) * sizeof(uint64_t), hipMemcpyHostToDevice));
+    LBL_HIP_TRY(hipMalloc(&d_row, n * sizeof(uint16_t)));
+    std::unique_ptr<uint16_t, decltype(&hipFree)> g_row(d_row, &hipFree);
+    // zeroed entries past the last one, as for the words
+    LBL_HIP_TRY(hipMalloc(&sp->ent, (n + kEntryPad) * sizeof(uint64_t)));
+    sp->n_ent = n;
+    LBL_HIP_TRY(hipMemset(sp->ent + n, 0, kEntryPad * sizeof(uint64_t)));
+    hipLaunchKernelGGL(k_run_fill, grid, block, 0, nullptr, d_seg, d_start, n_seg, sp->row, sp->val, sp->ent, d_row);
+    LBL_HIP_TRY(hipGetLastError());
+    rows->resize(n);
+    LBL_HIP_TRY(hipMemcpy(rows->data(), d_row, n * sizeof(uint16_t), hipMemcpyDeviceToHost));
+    return LBL_OK;
+}
+
 lbl_status sparse_assemble(lbl_abs *a, std::vector<SparsePart> &parts)
 {
     const uint32_t W = a->n_words;
@@ -1743,20 +2145,33 @@ lbl_status sparse_assemble(lbl_abs *a, std::vector<SparsePart> &parts)
                           reinterpret_cast<const void *>(&k_label_direct<kTileWaves, 4>)})
         LBL_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDirectLds));
     LBL_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_label_tiles_batch<kTileWaves>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTileLds));
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBatchLds));
     LBL_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_label_tiles_queue<kTileWaves>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTileLds));
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBatchLds));
+    LBL_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_label_runs<kTileWaves, uint64_t>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRunLds));
+    LBL_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_label_runs<kTileWaves, uint32_t>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRunLds32));
     const uint32_t n_cu = (uint32_t)device_cu_count();
     sp->tilings.resize(kNarrowTiling + 1);
     std::vector<uint16_t> rows_host(nnz);
-    if (nnz) LBL_HIP_TRY(hipMemcpy(rows_host.data(), sp->row, nnz * sizeof(uint16_t), hipMemcpyDeviceToHost));
+    std::vector<uint64_t> run_start;
+    {
+        const lbl_status st = make_runs(sp.get(), seg_start, &run_start, &rows_host);
+        if (st != LBL_OK) return st;
+    }
+    const bool runs = sp->ent != nullptr;
+    if (!runs && nnz)
+        LBL_HIP_TRY(hipMemcpy(rows_host.data(), sp->row, nnz * sizeof(uint16_t), hipMemcpyDeviceToHost));
+    const std::vector<uint64_t> &tile_start = runs ? run_start : seg_start;
+    const std::vector<double> costs = (runs ? run_costs : block_costs)(tile_start, rb_seg);
     for (int i = 0; i <= kNarrowTiling; ++i) {
         // the 32-bit mask kernel runs two tile workgroups per CU
         const bool one_frame = i == 0 || i == kNarrowTiling;
-        std::vector<uint32_t> k = one_frame ? choose_tiles(block_costs(seg_start, rb_seg), i == 0 ? n_cu : 2 * n_cu)
+        std::vector<uint32_t> k = one_frame ? choose_tiles(costs, i == 0 ? n_cu : 2 * n_cu)
                                             : std::vector<uint32_t>(sp->n_rb, 1u << (i - 1));
         TilingHost h;
-        make_tiling(seg_start, seg_word, rb_seg, k, &h);
+        (runs ? make_run_tiling : make_tiling)(tile_start, seg_word, rb_seg, k, &h);
         // the tile kernels address a task's entries (8 bytes each) and round
         // records with 32-bit byte offsets
         for (const SpTask &t : h.tasks)
@@ -1766,7 +2181,7 @@ lbl_status sparse_assemble(lbl_abs *a, std::vector<SparsePart> &parts)
         lbl_status st = upload_tiling(h, &sp->tilings[i], &sp->round_bytes);
         if (st != LBL_OK) return st;
         CompactHost c;
-        if (make_compact(h, rows_host, seg_start, rb_seg, a->n_traj, &c)) {
+        if (make_compact(h, rows_host, tile_start, rb_seg, a->n_traj, &c)) {
             st = upload_compact(c, &sp->tilings[i], &sp->round_bytes);
             if (st != LBL_OK) return st;
         }
@@ -1839,7 +2254,7 @@ namespace {
 
 // The three kernels of one frame with M-bit masks on tiling tl.
 template <typename M>
-lbl_status run_swm_t(const lbl_abs *a, const SpTiling &tl, size_t lds, const uint8_t *O, uint32_t n_props, void *ws,
+lbl_status run_swm_t(const lbl_abs *a, const SpTiling &tl, const uint8_t *O, uint32_t n_props, void *ws,
                      uint8_t *L, hipStream_t s, bool spans)
 {
     const SparseLayout &sp = *a->sp;
@@ -1849,14 +2264,25 @@ lbl_status run_swm_t(const lbl_abs *a, const SpTiling &tl, size_t lds, const uin
     auto span_end = [&](void *b, hipStream_t st, int kind) {
         if (spans) lbl::span_end(b, st, kind);
     };
+    const dim3 pack_grid((unsigned)(((uint64_t)sp.n_used * 64 + 255) / 256));
     void *spn = span_begin(s);
-    hipLaunchKernelGGL(k_pack_tables<M>, dim3((unsigned)(((uint64_t)sp.n_used * 64 + 255) / 256)), dim3(256), 0, s, O,
-                       n_props, sp.pack_first, a->nx, (uint32_t)a->order.morton, sp.used_words, sp.n_used, Tg);
+    if (sp.ent)
+        hipLaunchKernelGGL(k_pack_cells<M>, pack_grid, dim3(256), 0, s, O, n_props, sp.pack_first, a->nx,
+                           (uint32_t)a->order.morton, sp.used_words, sp.n_used, Tg);
+    else
+        hipLaunchKernelGGL(k_pack_tables<M>, pack_grid, dim3(256), 0, s, O, n_props, sp.pack_first, a->nx,
+                           (uint32_t)a->order.morton, sp.used_words, sp.n_used, Tg);
     LBL_HIP_TRY(hipGetLastError());
     span_end(spn, s, 0);
     spn = span_begin(s);
-    hipLaunchKernelGGL((k_label_tiles<kTileWaves, M>), dim3(tl.n_tiles), dim3(64 * kTileWaves), lds, s,
-                       tl.block_tile, tl.tasks_launch, tl.rounds, sp.row, sp.val, Tg, P, tl.tile_slot, tl.slot_row);
+    if (sp.ent)
+        hipLaunchKernelGGL((k_label_runs<kTileWaves, M>), dim3(tl.n_tiles), dim3(64 * kTileWaves),
+                           sizeof(M) == 8 ? kRunLds : kRunLds32, s, tl.block_tile, tl.tasks_launch, tl.rounds, sp.ent,
+                           Tg, P, tl.tile_slot, tl.slot_row);
+    else
+        hipLaunchKernelGGL((k_label_tiles<kTileWaves, M>), dim3(tl.n_tiles), dim3(64 * kTileWaves),
+                           sizeof(M) == 8 ? kTileLds : kTileLds32, s, tl.block_tile, tl.tasks_launch, tl.rounds,
+                           sp.row, sp.val, Tg, P, tl.tile_slot, tl.slot_row);
     LBL_HIP_TRY(hipGetLastError());
     span_end(spn, s, 1);
     spn = span_begin(s);
@@ -1914,8 +2340,8 @@ lbl_status run_swm(const lbl_abs *a, const uint8_t *O, uint32_t n_props, void *w
         return run_swm_direct<4>(a, O, n_props, ws, L, s, spans);
     }
     if (n_props <= 32 && (int)sp.tilings.size() > kNarrowTiling)
-        return run_swm_t<uint32_t>(a, sp.tilings[kNarrowTiling], kTileLds32, O, n_props, ws, L, s, spans);
-    return run_swm_t<uint64_t>(a, sp.tilings[0], kTileLds, O, n_props, ws, L, s, spans);
+        return run_swm_t<uint32_t>(a, sp.tilings[kNarrowTiling], O, n_props, ws, L, s, spans);
+    return run_swm_t<uint64_t>(a, sp.tilings[0], O, n_props, ws, L, s, spans);
 }
 
 }  // namespace lbl
