@@ -2,88 +2,141 @@
 // encoding: a cell's entry is 1 iff the region intersects the cell, read as
 // an overlap of positive area with the closed cell square).
 //
-// k_zero clears O; k_raster_shapes then gives every shape workgroups that
-// walk the cells of its bounding box (widened by one cell on each side, so
-// that rounding in the division cannot drop a cell, and clamped to the grid)
-// and test each cell exactly:
+// One workgroup takes a tile of 512 cells: it lists the shapes whose bounding
+// box meets the tile, then one lane per cell tests the listed shapes, collects
+// its propositions as a bit mask, and the wavefront writes its 64 cells' bytes
+// as one block.  Every byte of O is written once.  The tests are exact:
 //   rectangle: on both axes the overlap length, min of the upper ends minus
-//              max of the lower ends, is positive;
+//              max of the lower ends, is positive, that is, each of the two
+//              intervals starts before the other ends;
 //   disc:      the squared distance from the centre to the square's nearest
 //              point is below the squared radius.
 // Cell bounds are ix * cell and ix * cell + cell in double precision, and
 // products are not fused with sums, so every decision is the one the
-// definition gives in IEEE double arithmetic.  Shapes of one proposition may
-// write the same byte; they all write 1.
+// definition gives in IEEE double arithmetic.
+//
+// At 512 x 512 x 64 with 357 shapes (16.8 MB written, 2.4 us at the rate a
+// fill reaches) the kernel takes 10.0 us: 2.5 us of vector instructions, the
+// wait for the shapes, and the drain of the writes; 12.5-14 us per call with
+// the upload of the shapes (a 3 us copy).  Clearing O and then storing single
+// bytes, one workgroup group per shape, took 6.5 + 24 us, the bytes of a cell
+// lying 64 apart; 30-31 us per call.  Tiles of 256 cells: 10.3 us.
 #include <algorithm>
 #include <cmath>
 
+#include "emit.h"
 #include "lbl_internal.h"
 
 namespace lbl {
 namespace {
 
-constexpr uint32_t kRasterSlices = 8;  // workgroups per shape
+constexpr uint32_t kRasterWaves = 8;  // wavefronts per tile: 64 cells each
 
-unsigned zero_blocks(uint64_t n_bytes)
+// The cell coordinate in a z-order index: every second bit of z from bit 0
+// (y) or, of z >> 1, x.
+__device__ __forceinline__ uint32_t z_coord(uint32_t z)
 {
-    const uint64_t b = (n_bytes / 16 + 255) / 256;
-    return (unsigned)std::min<uint64_t>(std::max<uint64_t>(b, 1), 4096);
+    z &= 0x55555555u;
+    z = (z | (z >> 1)) & 0x33333333u;
+    z = (z | (z >> 2)) & 0x0F0F0F0Fu;
+    z = (z | (z >> 4)) & 0x00FF00FFu;
+    return (z | (z >> 8)) & 0xFFFFu;
 }
 
-// z-order index of cell (ix, iy): bits of ix at the odd positions, of iy at
-// the even ones (x the more significant bit of each pair).
-__device__ __forceinline__ uint32_t z_index(uint32_t ix, uint32_t iy)
-{
-    uint32_t z = 0;
-    for (int b = 0; b < 16; ++b) z |= ((ix >> b) & 1u) << (2 * b + 1) | ((iy >> b) & 1u) << (2 * b);
-    return z;
-}
+// A shape as the cells test it: a rectangle's ends on both axes, or a disc's
+// centre and squared radius.
+struct Listed {
+    double a, b, c, d;  // rectangle: x from a to b, y from c to d; disc: centre (a, b), c = radius squared
+};
 
-__global__ void __launch_bounds__(256) k_zero_bytes(uint8_t *__restrict__ O, uint64_t n)
-{
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if ((reinterpret_cast<uintptr_t>(O) & 15u) == 0) {
-        uint4 *o = reinterpret_cast<uint4 *>(O);
-        for (uint64_t i = i0; i < n / 16; i += stride) o[i] = make_uint4(0u, 0u, 0u, 0u);
-        for (uint64_t i = (n / 16) * 16 + i0; i < n; i += stride) O[i] = 0;
-    } else {
-        for (uint64_t i = i0; i < n; i += stride) O[i] = 0;
-    }
-}
-
-__global__ void __launch_bounds__(256)
-k_raster_shapes(const lbl_shape *__restrict__ shapes, uint32_t nx, uint32_t ny, double cell, uint32_t n_props,
-                uint32_t morton, uint8_t *__restrict__ O)
+// Tiles of 512 cells: with row-major ids 64 x 8 cells, wavefront w taking row
+// w of the tile; with z-order ids 512 consecutive ids (16 x 32 cells),
+// wavefront w taking ids 64 w ...
+__global__ void __launch_bounds__(64 * kRasterWaves)
+k_raster_tiles(const lbl_shape *__restrict__ shapes, uint32_t n_shapes, uint32_t nx, uint32_t ny, double cell,
+               uint32_t n_props, uint32_t morton, uint32_t n_tiles, uint8_t *__restrict__ O)
 {
 #pragma clang fp contract(off)
-    const lbl_shape sh = shapes[blockIdx.x];
-    const bool rect = sh.kind == LBL_SHAPE_RECT;
-    const double hx = sh.a, hy = rect ? sh.b : sh.a;
-    // bounding box in cells, widened by one and clamped (in double, so that
-    // far-away shapes do not overflow an integer)
-    const double fx0 = fmax(floor((sh.cx - hx) / cell) - 1.0, 0.0), fx1 = fmin(floor((sh.cx + hx) / cell) + 1.0, nx - 1.0);
-    const double fy0 = fmax(floor((sh.cy - hy) / cell) - 1.0, 0.0), fy1 = fmin(floor((sh.cy + hy) / cell) + 1.0, ny - 1.0);
-    if (!(fx0 <= fx1 && fy0 <= fy1)) return;
-    const uint32_t ix0 = (uint32_t)fx0, iy0 = (uint32_t)fy0;
-    const uint32_t wx = (uint32_t)fx1 - ix0 + 1, wy = (uint32_t)fy1 - iy0 + 1;
-    const uint64_t n_box = (uint64_t)wx * wy;
-    for (uint64_t k = (uint64_t)blockIdx.y * blockDim.x + threadIdx.x; k < n_box;
-         k += (uint64_t)gridDim.y * blockDim.x) {
-        const uint32_t ix = ix0 + (uint32_t)(k % wx), iy = iy0 + (uint32_t)(k / wx);
+    constexpr uint32_t kMost = 64 * kRasterWaves;  // shapes looked at (and listed) at a time
+    __shared__ Listed list[kMost];
+    __shared__ uint32_t info[kMost];  // proposition, bit 31: rectangle
+    __shared__ uint32_t n_listed;
+    __shared__ uint32_t stage[kRasterWaves][kStageWords];
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        // the tile's cells [tx, tx + tw) x [ty, ty + th), this lane's cell, the
+        // id of the wavefront's first cell and its number of cells
+        uint32_t tx, ty, tw, th, ix, iy, n;
+        uint64_t id0;
+        if (morton) {
+            const uint32_t z0 = tile * kMost, z = z0 + threadIdx.x;
+            tx = z_coord(z0 >> 1);
+            ty = z_coord(z0);
+            tw = 16;
+            th = 32;
+            ix = z_coord(z >> 1);
+            iy = z_coord(z);
+            id0 = z0 + 64u * wave;
+            n = id0 < (uint64_t)nx * ny ? 64u : 0u;
+        } else {
+            const uint32_t across = (nx + 63) / 64;
+            tx = tile % across * 64u;
+            ty = tile / across * kRasterWaves;
+            tw = 64;
+            th = kRasterWaves;
+            ix = tx + lane;
+            iy = ty + wave;
+            id0 = (uint64_t)iy * nx + tx;
+            n = min(64u, nx - tx);  // ny is a multiple of 8
+        }
         const double x0 = (double)ix * cell, x1 = x0 + cell;
         const double y0 = (double)iy * cell, y1 = y0 + cell;
-        bool hit;
-        if (rect) {
-            const double ox = fmin(x1, sh.cx + sh.a) - fmax(x0, sh.cx - sh.a);
-            const double oy = fmin(y1, sh.cy + sh.b) - fmax(y0, sh.cy - sh.b);
-            hit = ox > 0.0 && oy > 0.0;
-        } else {
-            const double qx = fmin(fmax(sh.cx, x0), x1), qy = fmin(fmax(sh.cy, y0), y1);
-            const double ex = sh.cx - qx, ey = sh.cy - qy;
-            hit = ex * ex + ey * ey < sh.a * sh.a;
+        const double tx0 = (double)tx * cell, tx1 = (double)(tx + tw - 1) * cell + cell;
+        const double ty0 = (double)ty * cell, ty1 = (double)(ty + th - 1) * cell + cell;
+        uint64_t mask = 0;
+        for (uint32_t s0 = 0; s0 < n_shapes; s0 += kMost) {
+            if (threadIdx.x == 0) n_listed = 0;
+            __syncthreads();
+            const uint32_t s = s0 + threadIdx.x;
+            if (s < n_shapes) {
+                const lbl_shape sh = shapes[s];
+                const bool rect = sh.kind == LBL_SHAPE_RECT;
+                const double hx = sh.a, hy = rect ? sh.b : sh.a;
+                const double xl = sh.cx - hx, xh = sh.cx + hx, yl = sh.cy - hy, yh = sh.cy + hy;
+                // on both axes the shape must start before the tile's last
+                // cell ends and end after its first cell starts: a cell that
+                // the tests below accept lies between the same rounded ends
+                bool in = xl <= tx1 && tx0 <= xh && yl <= ty1 && ty0 <= yh;
+                if (rect) in = in && xl < xh && yl < yh;  // without an inside it overlaps nothing
+                if (in) {
+                    const uint32_t i = atomicAdd(&n_listed, 1u);  // < kMost: one per thread
+                    list[i] = rect ? Listed{xl, xh, yl, yh} : Listed{sh.cx, sh.cy, sh.a * sh.a, 0.0};
+                    info[i] = sh.prop | (rect ? 0x80000000u : 0u);
+                }
+            }
+            __syncthreads();
+            const uint32_t m = n_listed;
+            for (uint32_t i = 0; i < m; ++i) {
+                const uint32_t f = (uint32_t)__builtin_amdgcn_readfirstlane((int)info[i]);
+                const Listed q = list[i];
+                bool hit;
+                if (f >> 31) {
+                    hit = q.a < x1 && x0 < q.b && q.c < y1 && y0 < q.d;
+                } else {
+                    const double ex = q.a - fmin(fmax(q.a, x0), x1), ey = q.b - fmin(fmax(q.b, y0), y1);
+                    hit = ex * ex + ey * ey < q.c;
+                }
+                mask |= hit ? 1ull << (f & 63u) : 0ull;
+            }
+            __syncthreads();  // the list is filled again
         }
-        if (hit) O[(morton ? (uint64_t)z_index(ix, iy) : (uint64_t)iy * nx + ix) * n_props + sh.prop] = 1;
+        uint8_t *dst = O + id0 * n_props;
+        if (n == 0) continue;  // whole wavefronts (every barrier is behind them)
+        if ((n_props & 15u) == 0 && (reinterpret_cast<uintptr_t>(O) & 15u) == 0)
+            emit_units(lane, n, mask, dst, n_props / 16);
+        else
+            emit_block(stage[wave], lane, n, mask, dst, n_props);
     }
 }
 
@@ -114,17 +167,21 @@ lbl_status lbl_raster_frame(const lbl_grid *g, double cell_m, const lbl_shape *s
         LBL_REQUIRE(s.a >= 0.0 && (s.kind == LBL_SHAPE_DISC || s.b >= 0.0), "shape sizes must be non-negative");
     }
     hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-    const uint64_t n_bytes = (uint64_t)g->nx * g->ny * n_props;
-    hipLaunchKernelGGL(k_zero_bytes, dim3(zero_blocks(n_bytes)), dim3(256), 0, st, O, n_bytes);
-    LBL_HIP_TRY(hipGetLastError());
-    if (n_shapes == 0) return LBL_OK;
-    void *ws = nullptr;
-    lbl_status rc = workspace(st, n_shapes * sizeof(lbl_shape), &ws);
-    if (rc != LBL_OK) return rc;
-    lbl_shape *d_shapes = static_cast<lbl_shape *>(ws);
-    LBL_HIP_TRY(hipMemcpyAsync(d_shapes, shapes, n_shapes * sizeof(lbl_shape), hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(k_raster_shapes, dim3((unsigned)n_shapes, kRasterSlices), dim3(256), 0, st, d_shapes, g->nx,
-                       g->ny, cell_m, n_props, (uint32_t)(g->cell_order == LBL_MORTON), O);
+    lbl_shape *d_shapes = nullptr;
+    if (n_shapes) {
+        void *ws = nullptr;
+        lbl_status rc = workspace(st, n_shapes * sizeof(lbl_shape), &ws);
+        if (rc != LBL_OK) return rc;
+        d_shapes = static_cast<lbl_shape *>(ws);
+        LBL_HIP_TRY(hipMemcpyAsync(d_shapes, shapes, n_shapes * sizeof(lbl_shape), hipMemcpyHostToDevice, st));
+    }
+    const bool morton = g->cell_order == LBL_MORTON;
+    const uint64_t n_cells = (uint64_t)g->nx * g->ny;
+    const uint64_t tiles = morton ? (n_cells + 64 * kRasterWaves - 1) / (64 * kRasterWaves)
+                                  : (uint64_t)((g->nx + 63) / 64) * (g->ny / kRasterWaves);
+    hipLaunchKernelGGL(k_raster_tiles, dim3((unsigned)std::min<uint64_t>(tiles, 1u << 20)), dim3(64 * kRasterWaves), 0,
+                       st, d_shapes, (uint32_t)n_shapes, g->nx, g->ny, cell_m, n_props, (uint32_t)morton,
+                       (uint32_t)tiles, O);
     LBL_HIP_TRY(hipGetLastError());
     return LBL_OK;
 }

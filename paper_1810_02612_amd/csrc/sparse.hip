@@ -52,6 +52,7 @@
 #include <queue>
 
 #include "batch.h"
+#include "emit.h"
 #include "profile.h"
 #include "runs.h"
 #include "sparse.h"
@@ -209,12 +210,7 @@ k_run_fill(const uint64_t *__restrict__ seg, const uint64_t *__restrict__ run_se
 
 // ---------------------------------------------------------------- per frame
 
-// Native vector types: loads and stores of these through address-space
-// qualified pointers compile (HIP's vector structs assign only in the
-// generic address space).
 typedef unsigned long long v2u64 __attribute__((ext_vector_type(2)));
-typedef unsigned int v4u32 __attribute__((ext_vector_type(4)));
-
 
 // One wavefront per word, one lane per cell: the mask of the propositions
 // cell (w, lane) meets, then the word's nibble tables Tg[w * 256 ..].
@@ -980,55 +976,6 @@ __device__ __forceinline__ uint64_t row_slots_or(const M *__restrict__ P, const 
     return bits;
 }
 
-// The label bytes of rows [t0, t0 + n) of one job (n <= 64), written as one
-// contiguous block L[t0 * np .. (t0 + n) * np): lane r holds the job's bits
-// of row t0 + r in v (bit p = proposition p).  The block is staged in LDS at
-// its offset modulo 16 (each lane ORs its row's bytes into 4-byte-aligned
-// words; neighbouring rows share the words at their boundary), then written
-// with 16-byte stores; the units at the block's two ends, which also hold
-// bytes of other rows, are written byte by byte, so no byte outside the
-// block is stored.  stage: 64 * 64 + 32 bytes of this wavefront's LDS (the
-// last row's words reach at most 2 bytes past the block).
-__device__ __forceinline__ void emit_block(uint32_t *stage, uint32_t lane, uint32_t n, uint64_t v, uint8_t *dst,
-                                           uint32_t np)
-{
-    const uintptr_t base = reinterpret_cast<uintptr_t>(dst);
-    const uint32_t mis = (uint32_t)(base & 15u);
-    const uint32_t total = mis + n * np;  // staged bytes, <= 15 + 4096
-    const uint32_t n_units = (total + 15) >> 4;
-    v4u32 *st4 = reinterpret_cast<v4u32 *>(stage);
-    for (uint32_t u = lane; u < n_units; u += 64) st4[u] = v4u32{0u, 0u, 0u, 0u};
-    __builtin_amdgcn_wave_barrier();
-    if (lane < n) {
-        const uint32_t o = mis + lane * np;
-        const uint32_t sh = 8 * (o & 3u);
-        uint32_t *w = stage + (o >> 2);
-        const uint32_t nq = ((o & 3u) + np + 3) >> 2;
-        uint32_t prev = 0;
-        for (uint32_t q = 0; q < nq; ++q) {
-            const uint32_t cur = 4 * q < np ? spread_nib((uint32_t)(v >> (4 * q)) & 0xFu) : 0u;
-            const uint32_t out = sh ? (cur << sh) | (prev >> (32 - sh)) : cur;
-            __hip_atomic_fetch_or(w + q, out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-            prev = cur;
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    // device memory (flat stores would also count on the LDS wait counter)
-    __attribute__((address_space(1))) uint8_t *g = (__attribute__((address_space(1))) uint8_t *)(dst - mis);
-    for (uint32_t u = lane; u < n_units; u += 64) {
-        const v4u32 x = st4[u];
-        const uint32_t lo = 16 * u, hi = lo + 16;
-        if (lo >= mis && hi <= total) {
-            *(__attribute__((address_space(1))) v4u32 *)(g + lo) = x;
-        } else {
-            const uint32_t xs[4] = {x.x, x.y, x.z, x.w};
-            for (uint32_t b = 0; b < 16; ++b)
-                if (lo + b >= mis && lo + b < total) g[lo + b] = (uint8_t)(xs[b >> 2] >> (8 * (b & 3u)));
-        }
-    }
-    __builtin_amdgcn_wave_barrier();  // the stage is reused by the next block
-}
-
 // A job's descriptor with every field in scalar registers (read through a
 // pointer held in the batch's descriptors, the fields would otherwise land in
 // vector registers and make the loops over them lane-divergent).
@@ -1045,10 +992,6 @@ __device__ __forceinline__ SegDesc uniform_seg(const SegDesc *segs, uint32_t i)
     return r;
 }
 
-// LDS of one wavefront's label-byte staging (emit_block): 64 rows of at
-// most 64 bytes at an offset below 16, plus the word a row's last bytes may
-// spill into.
-constexpr uint32_t kStageWords = (64 * 64 + 32) / 4;
 static_assert(kTileWaves * kStageWords * 4 <= kTileWaves * kRing * kTabWords * 8,
               "label staging must fit in the tile's table slots");
 
@@ -1307,9 +1250,7 @@ __device__ __forceinline__ uint64_t row_partials(const M *__restrict__ P, const 
 __global__ void __launch_bounds__(64)
 k_combine_batch(const GroupDesc *__restrict__ groups, const CombineItem *__restrict__ items)
 {
-    // 64 rows of at most 64 bytes at an offset below 16, plus the word a
-    // row's last bytes may spill into
-    __shared__ uint32_t stage[(64 * 64 + 32) / 4];
+    __shared__ uint32_t stage[kStageWords];
     const uint32_t lane = threadIdx.x;
     const CombineItem it = items[blockIdx.x];
     const GroupDesc &g = groups[it.group];
@@ -1345,13 +1286,12 @@ k_combine(const M *__restrict__ P, const uint32_t *__restrict__ rb_tile,
           const uint32_t *__restrict__ row_slot_off, const uint32_t *__restrict__ row_slots, uint64_t n_traj,
           uint32_t n_props, uint8_t *__restrict__ L)
 {
-    __shared__ uint32_t stage[4][(64 * 64 + 32) / 4];
+    __shared__ uint32_t stage[4][kStageWords];
     const bool v16 = (n_props & 15u) == 0 && (reinterpret_cast<uintptr_t>(L) & 15u) == 0;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t n_waves = ((uint64_t)gridDim.x * blockDim.x) >> 6;
     const uint64_t n_groups = (n_traj + 63) / 64;
     const uint32_t upr = n_props / 16;  // 16-byte units per row: 1 .. 4
-    const uint32_t shift = upr == 1 ? 0 : upr == 2 ? 1 : upr == 4 ? 2 : 32;  // 32: not a power of two
     for (uint64_t grp = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; grp < n_groups; grp += n_waves) {
         const uint64_t t0 = grp * 64, t = t0 + lane;
         uint64_t bits = 0;
@@ -1362,20 +1302,7 @@ k_combine(const M *__restrict__ P, const uint32_t *__restrict__ rb_tile,
             emit_block(stage[wave], lane, n, bits, L + t0 * n_props, n_props);
             continue;
         }
-        const uint32_t units = n * upr;
-        uint4 *dst = reinterpret_cast<uint4 *>(L + t0 * n_props);
-        // uniform trip count: every lane takes part in the shuffles
-        for (uint32_t ub = 0; ub < units; ub += 64) {
-            const uint32_t u = ub + lane;  // < 64 * upr, so row < 64
-            const uint32_t row = min(shift < 32 ? u >> shift : u / upr, 63u);
-            const uint32_t c = u - row * upr;
-            const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)bits, (int)row);
-            const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(bits >> 32), (int)row);
-            const uint32_t b = (uint32_t)((((uint64_t)hi << 32) | lo) >> (16 * c)) & 0xFFFFu;
-            if (u < units)
-                dst[u] = make_uint4(spread_nib(b & 0xFu), spread_nib((b >> 4) & 0xFu), spread_nib((b >> 8) & 0xFu),
-                                    spread_nib(b >> 12));
-        }
+        emit_units(lane, n, bits, L + t0 * n_props, upr);
     }
 }
 
