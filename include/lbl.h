@@ -465,14 +465,13 @@ lbl_status lbl_cell_position(const lbl_grid *grid, uint32_t cell, uint32_t *word
  *                        pred = 0xFFFFFFFF at the start.  Following pred
  *                        from any reached vertex leads back to the start.
  *   n_sweeps             optional: relaxation sweeps up to and including
- *                        the first that changed nothing (at most n_vertices *
- *                        n_states + 1; up to three more run, changing
- *                        nothing, since sweeps go in groups of four between
- *                        reads of their flags).
+ *                        the first that brought no vertex nearer (at most
+ *                        n_vertices * n_states + 1; a few more are enqueued
+ *                        ahead and change nothing).
  *
  * Synchronous: enqueued on hip_stream (0 = the null stream), returns when the
- * outputs are written.  Uses the stream's workspace (8 bytes per product
- * vertex).  Errors: LBL_EINVAL for a null pointer, a size or state out of
+ * outputs are written; the host polls meanwhile.  Uses the stream's workspace
+ * (8 bytes per product vertex, a byte per edge, 3 bytes per vertex).  Errors: LBL_EINVAL for a null pointer, a size or state out of
  * range, l_stride < n_props, a delta entry that is neither a state nor LBL_MONITOR_REJECT, or an
  * edge whose vertex is out of range or whose cost is 0 (found on the device;
  * dist and pred are then unspecified); LBL_ENOMEM; LBL_EDEVICE.

@@ -64,6 +64,7 @@ struct WsBuf {
     void *p = nullptr;
     size_t n = 0;
     int device = -1;
+    void *pinned = nullptr;  // kPinnedBytes of host memory that kernels can write
 };
 std::mutex g_ws_mu;
 std::unordered_map<hipStream_t, WsBuf> g_ws;
@@ -81,7 +82,9 @@ lbl_status workspace(hipStream_t s, size_t bytes, void **out)
         if (b.device != dev) LBL_HIP_TRY(hipSetDevice(b.device));
         (void)hipFree(b.p);
         if (b.device != dev) LBL_HIP_TRY(hipSetDevice(cur));
-        b = WsBuf{};
+        b.p = nullptr;
+        b.n = 0;
+        b.device = -1;
     }
     if (!b.p) {
         size_t n = std::max<size_t>(bytes, 1u << 20);
@@ -91,6 +94,16 @@ lbl_status workspace(hipStream_t s, size_t bytes, void **out)
         b.device = dev;
     }
     *out = b.p;
+    return LBL_OK;
+}
+
+lbl_status pinned_flags(hipStream_t s, void **host)
+{
+    std::lock_guard<std::mutex> lk(g_ws_mu);
+    WsBuf &b = g_ws[s];
+    // portable: the stream's device may change with its handle's reuse
+    if (!b.pinned) LBL_HIP_TRY(hipHostMalloc(&b.pinned, kPinnedBytes, hipHostMallocPortable | hipHostMallocMapped));
+    *host = b.pinned;
     return LBL_OK;
 }
 

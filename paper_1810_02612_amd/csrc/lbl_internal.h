@@ -87,6 +87,11 @@ namespace lbl {
 // Per-stream scratch memory, grown on demand (growth synchronizes the stream).
 lbl_status workspace(hipStream_t s, size_t bytes, void **out);
 
+// Per-stream pinned host memory (kPinnedBytes, kept with the workspace) that
+// kernels on that stream can write and the host can poll.
+constexpr size_t kPinnedBytes = 4096;
+lbl_status pinned_flags(hipStream_t s, void **host);
+
 // ---------------------------------------------------------------- kernels
 
 // Kernel choices (runtime representation of LBL_KERNEL_*).

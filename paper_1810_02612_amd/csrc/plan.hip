@@ -4,17 +4,31 @@
 // on the label of e.  A monitor with no move for a label has met a bad
 // prefix, so that product edge is absent.
 //
-// Bellman-Ford on the device: every sweep relaxes each (edge, state) pair
-// once, with a 64-bit atomic minimum of (distance << 32 | product edge id),
-// until a sweep changes nothing.  Values only decrease and each is the cost
-// of a real path, so the fixpoint holds the shortest distances, and in the
-// low word the smallest product edge id among the edges on a shortest path
-// into the vertex.  Costs are at least 1, so predecessors always have a
-// smaller distance and the predecessor graph is a tree.  A graph with n
-// product vertices needs at most n sweeps (each kernel ends; the host loop
-// is bounded).  Sweeps run in groups of kGroup between reads of their flags
-// (a sweep after the fixpoint changes nothing, so the extra ones are
-// harmless), which saves a host synchronization per sweep.
+// Bellman-Ford on the device: a sweep relaxes the (edge, state) pairs of every
+// edge whose source vertex came nearer in the sweep before, with a 64-bit
+// atomic minimum of (distance << 32 | product edge id), until a sweep brings
+// no vertex nearer.  Values only decrease and each is the cost of a real
+// path, and every edge is relaxed with its source's final distance, so the
+// fixpoint holds the shortest distances, and in the low word the smallest
+// product edge id among the edges on a shortest path into the vertex.  Costs
+// are at least 1, so predecessors always have a smaller distance and the
+// predecessor graph is a tree.  A graph with n product vertices needs at most
+// n sweeps (each kernel ends; the host loop is bounded).
+//
+// A sweep reads 4 bytes of every edge and a byte per vertex; only the few
+// edges that leave a changed vertex read more.  What a call costs beyond that
+// is launches and waits, so the host does not wait between sweeps: it keeps
+// kAhead of them enqueued and reads in pinned memory, where each sweep reports
+// on the one before, whether that one changed anything.  The sweep after the
+// first that did not writes the outputs, the ones after it do nothing.
+//
+// 568,958 transitions, 2 states, 16 to 17 sweeps: 179 us per call, 256 when
+// every sweep relaxed every reached edge and the host waited for each group
+// of four.  A sweep is bound by its chain of loads (5 us where little
+// changes, 2.3 when nothing is left) and by atomics on shared vertices in the
+// middle of the search (up to 14 us); changed vertices as bits set by atomics
+// took up to 37 us there, reading an edge's fields one after the other 9.0
+// instead of 7.1 us on average.
 #include <algorithm>
 
 #include "lbl_internal.h"
@@ -22,67 +36,164 @@
 namespace lbl {
 namespace {
 
+constexpr uint32_t kInf = 0xFFFFFFFFu;
 constexpr uint64_t kNone = ~0ull;
-constexpr uint32_t kGroup = 4;  // sweeps per read of the flags
+constexpr uint32_t kAhead = 4;    // sweeps enqueued beyond the last one reported on
+constexpr uint32_t kReports = 64; // report slots, used in turn (more than kAhead)
+constexpr uint32_t kMaxDelta = 8u << 8;
 
-__global__ void __launch_bounds__(256) k_plan_init(uint64_t *__restrict__ best, uint64_t n, uint64_t start)
+struct Delta {
+    uint8_t move[kMaxDelta];
+};
+
+// What the kernels of one call share.
+struct PlanArgs {
+    const uint32_t *src, *dst, *cost;
+    uint64_t n_vertices, n_edges, start;
+    uint32_t n_props, n_states;
+    uint64_t *best;       // [n_vertices * n_states]
+    // byte per vertex (set by plain stores: bits would need atomics on the few
+    // words that a frontier shares), in dwords: sweep k reads [k % 3], sets
+    // [(k + 1) % 3], clears [(k + 2) % 3]
+    uint32_t *near[3];
+    uint32_t near_words;
+    uint8_t *delta;       // the monitor's moves
+    uint8_t *sigma;       // [n_edges] labels as bit sets
+    uint32_t *changed;    // [4] whether sweep k brought a vertex nearer: [k % 4]
+    uint64_t *report;     // pinned: [kReports] of sweep k: 2 (k + 1) + changed; [kReports]: an edge is invalid
+    uint32_t *dist, *pred;
+};
+
+__device__ __forceinline__ void to_host(uint64_t *p, uint64_t v)
 {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-        best[i] = i == start ? 0xFFFFFFFFull : kNone;  // start: distance 0, no predecessor
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// flags[0]: some value decreased; flags[1]: an edge names a vertex out of
-// range or has cost 0.
-__global__ void __launch_bounds__(256)
-k_plan_relax(const uint32_t *__restrict__ src, const uint32_t *__restrict__ dst, const uint32_t *__restrict__ cost,
-             const uint8_t *__restrict__ L, uint32_t l_stride, uint32_t n_props, uint32_t n_states,
-             const uint8_t *__restrict__ delta,
-             uint64_t n_vertices, uint64_t n_edges, uint64_t start, uint64_t *__restrict__ best,
-             uint32_t *__restrict__ flags)
+__device__ __forceinline__ bool edge_ok(const PlanArgs &p, uint32_t u, uint32_t v, uint32_t c)
 {
-    bool changed = false, bad = false;
-    for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n_edges;
-         e += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t u = src[e], v = dst[e], c = cost[e];
-        if (u >= n_vertices || v >= n_vertices || c == 0) {
-            bad = true;
-            continue;
-        }
+    return u < p.n_vertices && v < p.n_vertices && c != 0;
+}
+
+__global__ void __launch_bounds__(256) k_plan_init(PlanArgs p, Delta delta, uint32_t n_delta,
+                                                   const uint8_t *__restrict__ L, uint32_t l_stride)
+{
+    const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
+    const uint64_t n = p.n_vertices * p.n_states;
+    const uint32_t v0 = (uint32_t)(p.start / p.n_states);
+    for (uint64_t i = i0; i < n; i += step) p.best[i] = i == p.start ? (uint64_t)kInf : kNone;  // start: distance 0, no predecessor
+    for (uint64_t i = i0; i < p.near_words; i += step) {
+        p.near[0][i] = i == v0 / 4 ? 1u << (8 * (v0 % 4)) : 0u;
+        p.near[1][i] = 0;
+        p.near[2][i] = 0;
+    }
+    if (blockIdx.x == 0) {
+        for (uint32_t i = threadIdx.x; i < n_delta; i += blockDim.x) p.delta[i] = delta.move[i];
+        if (threadIdx.x < 4) p.changed[threadIdx.x] = 0;
+    }
+    bool bad = false;
+    for (uint64_t e = i0; e < p.n_edges; e += step) {
+        bad = bad || !edge_ok(p, p.src[e], p.dst[e], p.cost[e]);
         uint32_t sigma = 0;  // the label as a proposition bit set
-        for (uint32_t p = 0; p < n_props; ++p) sigma |= (L[e * l_stride + p] != 0 ? 1u : 0u) << p;
-        for (uint32_t q = 0; q < n_states; ++q) {
-            const uint64_t du = best[(uint64_t)u * n_states + q] >> 32;
-            if (du == 0xFFFFFFFFull) continue;  // not reached yet
-            const uint32_t q2 = delta[(q << n_props) | sigma];
-            if (q2 >= n_states) continue;  // the monitor rejects: no product edge
-            const uint64_t nd = du + c;
-            if (nd >= 0xFFFFFFFFull) continue;  // beyond the representable costs
-            const uint64_t to = (uint64_t)v * n_states + q2;
-            if (to == start) continue;  // the start keeps distance 0 and no predecessor
-            const uint64_t cand = (nd << 32) | (e * n_states + q);
-            // values only decrease: a candidate no better than a value read
-            // now cannot win, and most relaxations after the first sweeps are
-            // such (their atomic would only cost time)
-            if (cand >= best[to]) continue;
-            const unsigned long long old = atomicMin(reinterpret_cast<unsigned long long *>(best + to), cand);
-            changed = changed || cand < old;
-        }
+        for (uint32_t q = 0; q < p.n_props; ++q) sigma |= (L[e * l_stride + q] != 0 ? 1u : 0u) << q;
+        p.sigma[e] = (uint8_t)sigma;
     }
-    // one atomic per wavefront that saw a change (vector atomics only)
-    const uint64_t any_changed = __ballot(changed), any_bad = __ballot(bad);
-    const uint32_t lane = threadIdx.x & 63;
-    if (any_changed && lane == (uint32_t)__builtin_ctzll(any_changed)) atomicOr(flags + 0, 1u);
-    if (any_bad && lane == (uint32_t)__builtin_ctzll(any_bad)) atomicOr(flags + 1, 1u);
+    if (bad) to_host(p.report + kReports, 1);
 }
 
-__global__ void __launch_bounds__(256)
-k_plan_unpack(const uint64_t *__restrict__ best, uint64_t n, uint32_t *__restrict__ dist, uint32_t *__restrict__ pred)
+// best[to] = min(best[to], cand).  Where many lanes have the same target (the
+// sink vertices of a roadmap end thousands of edges, and atomics on one
+// address go one by one), their minimum is formed in the wavefront first.
+__device__ __forceinline__ void best_min(uint64_t *best, uint64_t to, uint64_t cand)
 {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t b = best[i];
-        dist[i] = (uint32_t)(b >> 32);
-        pred[i] = (uint32_t)b;
+    const uint64_t here = __ballot(true);
+    const int lead = __builtin_ctzll(here);
+    const uint64_t t0 = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)to) |
+                        ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(to >> 32)) << 32);
+    const uint64_t same = __ballot(to == t0);
+    if (__popcll(same) >= 8) {
+        if (to == t0) {
+            for (uint64_t left = same & (same - 1ull); left; left &= left - 1ull) {
+                const int l = __builtin_ctzll(left);
+                const uint64_t c = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)cand, l) |
+                                   ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(cand >> 32), l) << 32);
+                cand = c < cand ? c : cand;
+            }
+            if ((int)(threadIdx.x & 63) != lead) return;
+        }
     }
+    atomicMin(reinterpret_cast<unsigned long long *>(best + to), (unsigned long long)cand);
+}
+
+// Sweep k, for monitors of at most S states.  A sweep is a chain of loads that
+// wait for each other, so as many as can go together do: the edge's four
+// fields; then its source's flag and distances; then the distances its
+// candidates would replace.  Whether a candidate brings its vertex nearer is
+// judged by the value read, which may be older and larger than the current
+// one (the vertex is then relaxed once more, to no effect), so nothing waits
+// for the atomic minimum.
+template <int S>
+__global__ void __launch_bounds__(256) k_plan_sweep(PlanArgs p, uint64_t k)
+{
+    __shared__ uint8_t moves[S << 8];
+    const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
+    const bool ended = k > 0 && p.changed[(k + 3) % 4] == 0;  // the sweep before changed nothing
+    if (i0 == 0) {
+        if (k > 0) to_host(p.report + (k - 1) % kReports, 2 * k + (ended ? 0 : 1));
+        p.changed[(k + 1) % 4] = 0;
+    }
+    if (ended) {
+        // the first sweep after the fixpoint writes the outputs
+        if (k == 1 || p.changed[(k + 2) % 4] != 0)
+            for (uint64_t i = i0; i < p.n_vertices * p.n_states; i += step) {
+                const uint64_t b = p.best[i];
+                p.dist[i] = (uint32_t)(b >> 32);
+                p.pred[i] = (uint32_t)b;
+            }
+        return;
+    }
+    const uint8_t *now = reinterpret_cast<const uint8_t *>(p.near[k % 3]);
+    uint8_t *next = reinterpret_cast<uint8_t *>(p.near[(k + 1) % 3]);
+    uint32_t *clear = p.near[(k + 2) % 3];
+    for (uint32_t i = threadIdx.x; i < p.n_states << p.n_props; i += blockDim.x) moves[i] = p.delta[i];
+    for (uint64_t i = i0; i < p.near_words; i += step) clear[i] = 0;
+    __syncthreads();
+    bool changed = false;
+    for (uint64_t e = i0; e < p.n_edges; e += step) {
+        const uint32_t u = p.src[e], v = p.dst[e], c = p.cost[e], sigma = p.sigma[e];
+        if (!edge_ok(p, u, v, c)) continue;
+        const uint8_t active = now[u];
+        uint32_t du[S];
+#pragma unroll
+        for (int q = 0; q < S; ++q) du[q] = (uint32_t)(p.best[(uint64_t)u * p.n_states + min((uint32_t)q, p.n_states - 1)] >> 32);
+        if (!active) continue;
+        uint64_t cand[S], to[S], old[S];
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const uint32_t q2 = (uint32_t)q < p.n_states ? moves[((uint32_t)q << p.n_props) | sigma] : p.n_states;
+            const uint64_t nd = (uint64_t)du[q] + c;
+            to[q] = (uint64_t)v * p.n_states + min(q2, p.n_states - 1);
+            // no product edge: the source is not reached, the monitor
+            // rejects, the cost cannot be represented, or it ends at the
+            // start, which keeps distance 0 and no predecessor
+            const bool edge = du[q] != kInf && q2 < p.n_states && nd < kInf && to[q] != p.start;
+            cand[q] = edge ? (nd << 32) | (e * p.n_states + q) : kNone;
+            old[q] = p.best[to[q]];
+        }
+        bool nearer = false;
+#pragma unroll
+        for (int q = 0; q < S; ++q)
+            if (cand[q] < old[q]) {  // values only decrease: otherwise it cannot win
+                best_min(p.best, to[q], cand[q]);
+                // a smaller edge id at the same distance changes no neighbour
+                nearer = nearer || cand[q] >> 32 < old[q] >> 32;
+            }
+        if (nearer) {
+            changed = true;
+            next[v] = 1;
+        }
+    }
+    const uint64_t any = __ballot(changed);  // one atomic per wavefront that saw a change
+    if (any && (threadIdx.x & 63) == (uint32_t)__builtin_ctzll(any)) atomicOr(p.changed + k % 4, 1u);
 }
 
 unsigned blocks_for(uint64_t n) { return (unsigned)std::min<uint64_t>(std::max<uint64_t>((n + 255) / 256, 1), 8192); }
@@ -118,41 +229,87 @@ extern "C" lbl_status lbl_product_shortest_paths(uint64_t n_vertices, uint64_t n
     LBL_HIP_TRY(hipGetDevice(&cur));
 
     const uint64_t n = n_vertices * n_states;
+    const uint64_t near_words = (n_vertices + 3) / 4;
     auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
-    void *ws = nullptr;
-    lbl_status st = workspace(s, up(n * sizeof(uint64_t)) + up(n_delta) + up(2 * kGroup * sizeof(uint32_t)), &ws);
+    void *ws = nullptr, *pin = nullptr;
+    lbl_status st = workspace(s, up(n * sizeof(uint64_t)) + 3 * up(near_words * 4) + up(n_delta) + up(n_edges) + 256, &ws);
     if (st != LBL_OK) return st;
-    uint64_t *best = static_cast<uint64_t *>(ws);
-    uint8_t *d_delta = reinterpret_cast<uint8_t *>(ws) + up(n * sizeof(uint64_t));
-    uint32_t *d_flags = reinterpret_cast<uint32_t *>(d_delta + up(n_delta));
-    LBL_HIP_TRY(hipMemcpyAsync(d_delta, delta, n_delta, hipMemcpyHostToDevice, s));
-    const uint64_t start = (uint64_t)v0 * n_states + q0;
-    hipLaunchKernelGGL(k_plan_init, dim3(blocks_for(n)), dim3(256), 0, s, best, n, start);
+    st = pinned_flags(s, &pin);
+    if (st != LBL_OK) return st;
+    static_assert((kReports + 1) * sizeof(uint64_t) <= kPinnedBytes, "reports must fit the pinned memory");
+    volatile uint64_t *report = static_cast<volatile uint64_t *>(pin);
+    for (uint32_t i = 0; i <= kReports; ++i) report[i] = 0;
+    uint8_t *at = static_cast<uint8_t *>(ws);
+    auto take = [&](size_t bytes) {
+        uint8_t *r = at;
+        at += up(bytes);
+        return r;
+    };
+    PlanArgs p{};
+    p.src = src;
+    p.dst = dst;
+    p.cost = cost;
+    p.n_vertices = n_vertices;
+    p.n_edges = n_edges;
+    p.start = (uint64_t)v0 * n_states + q0;
+    p.n_props = n_props;
+    p.n_states = n_states;
+    p.best = reinterpret_cast<uint64_t *>(take(n * sizeof(uint64_t)));
+    for (uint32_t *&w : p.near) w = reinterpret_cast<uint32_t *>(take(near_words * 4));
+    p.near_words = (uint32_t)near_words;
+    p.delta = take(n_delta);
+    p.sigma = take(n_edges);
+    p.changed = reinterpret_cast<uint32_t *>(take(16));
+    void *dev_report = nullptr;
+    LBL_HIP_TRY(hipHostGetDevicePointer(&dev_report, pin, 0));
+    p.report = static_cast<uint64_t *>(dev_report);
+    p.dist = dist;
+    p.pred = pred;
+    Delta d{};
+    std::copy(delta, delta + n_delta, d.move);
+    hipLaunchKernelGGL(k_plan_init, dim3(blocks_for(std::max(n, n_edges))), dim3(256), 0, s, p, d, (uint32_t)n_delta, L,
+                       l_stride);
     LBL_HIP_TRY(hipGetLastError());
     // Bellman-Ford needs at most n sweeps before one that changes nothing
-    uint64_t sweeps = 0;
+    // (sweep n at the latest), and sweep n + 1 to report on it
+    uint64_t launched = 0, known = 0;  // sweeps enqueued; reported on
     bool done = false;
-    for (uint64_t run = 0; !done && run <= n; run += kGroup) {
-        LBL_HIP_TRY(hipMemsetAsync(d_flags, 0, 2 * kGroup * sizeof(uint32_t), s));
-        for (uint32_t j = 0; j < kGroup; ++j) {
-            hipLaunchKernelGGL(k_plan_relax, dim3(blocks_for(n_edges)), dim3(256), 0, s, src, dst, cost, L, l_stride,
-                               n_props, n_states, d_delta, n_vertices, n_edges, start, best, d_flags + 2 * j);
-            LBL_HIP_TRY(hipGetLastError());
+    uint32_t idle = 0;
+    const dim3 grid(blocks_for(n_edges));
+    const auto sweep = n_states <= 1 ? k_plan_sweep<1> : n_states <= 2 ? k_plan_sweep<2> : n_states <= 4 ? k_plan_sweep<4> : k_plan_sweep<8>;
+    while (!done && known <= n) {
+        if (launched < known + 1 + kAhead && launched < n + 2) {
+            hipLaunchKernelGGL(sweep, grid, dim3(256), 0, s, p, launched);
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess) {
+                (void)hipStreamSynchronize(s);  // the pinned memory and the caller's arrays are still in use
+                LBL_HIP_TRY(e);
+            }
+            ++launched;
+        } else if (++idle % 4096 == 0) {
+            // nothing for a while: a kernel that failed will never report
+            hipError_t e = hipStreamQuery(s);
+            if (e != hipErrorNotReady) {
+                LBL_HIP_TRY(e);
+                const uint64_t r = report[known % kReports];
+                LBL_REQUIRE(r >> 1 == known + 1, "the sweeps ended without a report");
+            }
         }
-        uint32_t h[2 * kGroup] = {};
-        LBL_HIP_TRY(hipMemcpyAsync(h, d_flags, sizeof(h), hipMemcpyDeviceToHost, s));
-        LBL_HIP_TRY(hipStreamSynchronize(s));
-        for (uint32_t j = 0; j < kGroup; ++j)
-            LBL_REQUIRE(h[2 * j + 1] == 0, "an edge names a vertex >= n_vertices or has cost 0");
-        for (uint32_t j = 0; j < kGroup && !done; ++j) {
-            ++sweeps;
-            done = h[2 * j] == 0;  // this sweep changed nothing: the fixpoint
+        for (;;) {
+            const uint64_t r = report[known % kReports];
+            if (r >> 1 != known + 1) break;
+            ++known;
+            idle = 0;
+            if (!(r & 1)) {
+                done = true;
+                break;
+            }
         }
     }
-    LBL_REQUIRE(done, "no fixpoint within the Bellman-Ford bound (cannot happen with costs >= 1)");
-    hipLaunchKernelGGL(k_plan_unpack, dim3(blocks_for(n)), dim3(256), 0, s, best, n, dist, pred);
-    LBL_HIP_TRY(hipGetLastError());
     LBL_HIP_TRY(hipStreamSynchronize(s));
+    LBL_REQUIRE(report[kReports] == 0, "an edge names a vertex >= n_vertices or has cost 0");
+    LBL_REQUIRE(done, "no fixpoint within the Bellman-Ford bound (cannot happen with costs >= 1)");
+    const uint64_t sweeps = known;
     if (n_sweeps) *n_sweeps = (uint32_t)std::min<uint64_t>(sweeps, 0xFFFFFFFFull);
     return LBL_OK;
 }
