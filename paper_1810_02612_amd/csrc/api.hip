@@ -438,7 +438,7 @@ lbl_status lbl_abstraction_info(lbl_abs_t a, lbl_abs_info *out)
     if (a->sp) {
         const SparseLayout &sp = *a->sp;
         const SpTiling &t = sp.tilings[0];
-        const uint64_t word_bytes = sp.nnz * (sizeof(uint16_t) + sizeof(uint64_t));
+        const uint64_t word_bytes = sp.val ? sp.nnz * (sizeof(uint16_t) + sizeof(uint64_t)) : 0;
         const uint64_t run_bytes = sp.n_ent * sizeof(uint64_t);
         // what the tile kernels read: run entries, or the words themselves
         const uint64_t entry_bytes = sp.ent ? run_bytes : word_bytes;
@@ -457,7 +457,10 @@ lbl_status lbl_abstraction_info(lbl_abs_t a, lbl_abs_info *out)
             out->sparse_tiles_narrow = u.n_tiles;
         }
         const DirectLayout &d = sp.direct;
-        if (d.chunks) {
+        if (sp.row_tiles) {
+            out->sparse_tiles_direct = sp.row_tiles->n_tiles;
+            out->sparse_frame_bytes_direct = sp.row_tiles->bytes();
+        } else if (d.n_tiles) {
             out->sparse_tiles_direct = d.n_tiles;
             out->sparse_frame_bytes_direct = word_bytes + d.n_chunks * sizeof(SpChunk) +
                                              d.n_parts * sizeof(DirectPart) + (d.n_tiles + 1ull) * sizeof(uint32_t);

@@ -5,6 +5,7 @@
 #include <vector>
 
 #include "lbl_internal.h"
+#include "rowtiles.h"
 #include "runs.h"
 
 namespace lbl {
@@ -93,7 +94,8 @@ struct DirectPart {
 // block (64 entries from the block's first, the block's last chunk
 // partial), in layout order, cut into n_tiles tiles of equal chunk counts;
 // a tile spanning row blocks has one part per block.  Tile t's parts are
-// tile_part[t] .. tile_part[t + 1].  Empty (no device arrays) when not built.
+// tile_part[t] .. tile_part[t + 1].  The device arrays are null when the ids
+// do not fit 32 bits (n_tiles is then 0) or row tiles label the layout.
 struct DirectLayout {
     uint32_t n_tiles = 0;
     uint32_t n_parts = 0;
@@ -146,6 +148,7 @@ struct SparseLayout {
     uint32_t n_rb = 0;
     uint64_t nnz = 0;            // entries (non-zero words of T)
     uint64_t n_segments = 0;     // non-empty (row block, word) segments
+    // (both null where run entries and row tiles hold them)
     uint16_t *row = nullptr;     // device [nnz] row within the row block
     uint64_t *val = nullptr;     // device [nnz] word value
     // Run entries (runs.h): the same segments, their words as run codes, and
@@ -160,8 +163,10 @@ struct SparseLayout {
     // tilings[1 + i]: 2^i tiles per row block (batches); tilings[kNarrowTiling]:
     // one frame of at most 32 propositions (about two tiles per CU)
     std::vector<SpTiling> tilings;
-    // the direct-mask kernel's tiles (frames of at most 4 propositions)
+    // frames of at most 4 propositions: the direct-mask kernel's tiles, or row
+    // tiles in their place
     DirectLayout direct;
+    std::unique_ptr<RowTiles> row_tiles;
     size_t round_bytes = 0;      // device bytes of all tilings' tables
     ~SparseLayout();
 };

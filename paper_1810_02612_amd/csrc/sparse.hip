@@ -1825,7 +1825,9 @@ static lbl_status upload_compact(const CompactHost &c, SpTiling *t, size_t *byte
     return LBL_OK;
 }
 
-static lbl_status upload_direct(const DirectHost &c, const std::vector<uint32_t> &seg_word, DirectLayout *d,
+// upload false: only the split's sizes, which say whether a frame takes the
+// direct kernels (takes_direct).
+static lbl_status upload_direct(const DirectHost &c, const std::vector<uint32_t> &seg_word, bool upload, DirectLayout *d,
                                 size_t *bytes)
 {
     // 32-bit chunk and segment ids: larger layouts keep the nibble kernels only
@@ -1835,6 +1837,7 @@ static lbl_status upload_direct(const DirectHost &c, const std::vector<uint32_t>
     d->n_parts = (uint32_t)c.parts.size();
     d->max_part_segs = 0;
     for (const DirectPart &p : c.parts) d->max_part_segs = std::max(d->max_part_segs, p.n_seg);
+    if (!upload) return LBL_OK;
     auto up = [](void **dst, const void *src, size_t n) -> hipError_t {
         hipError_t e = hipMalloc(dst, std::max<size_t>(n, 1));
         if (e == hipSuccess && n) e = hipMemcpy(*dst, src, n, hipMemcpyHostToDevice);
@@ -2115,10 +2118,21 @@ lbl_status sparse_assemble(lbl_abs *a, std::vector<SparsePart> &parts)
 
     }
     {
+        lbl_status st = build_row_tiles(a, *sp, seg_start, seg_word, rb_seg, &sp->row_tiles);
+        if (st != LBL_OK) return st;
+        if (sp->row_tiles) {
+            sp->round_bytes += sp->row_tiles->bytes();
+            if (runs) {  // no kernel reads the words in this order then
+                (void)hipFree(sp->row);
+                (void)hipFree(sp->val);
+                sp->row = nullptr;
+                sp->val = nullptr;
+            }
+        }
         // the direct-mask kernel's tiles: two workgroups per CU
         DirectHost dh;
         make_direct(seg_start, rb_seg, 2 * n_cu, &dh);
-        lbl_status st = upload_direct(dh, seg_word, &sp->direct, &sp->round_bytes);
+        st = upload_direct(dh, seg_word, !sp->row_tiles, &sp->direct, &sp->round_bytes);
         if (st != LBL_OK) return st;
     }
     LBL_HIP_TRY(hipDeviceSynchronize());
@@ -2143,7 +2157,7 @@ namespace {
 bool takes_direct(const SparseLayout &sp, uint32_t n_props, uint32_t *np)
 {
     *np = n_props <= 1 ? 1 : n_props <= 2 ? 2 : 4;
-    return n_props <= 4 && sp.direct.chunks != nullptr &&
+    return n_props <= 4 && sp.direct.n_tiles != 0 &&
            (size_t)sp.direct.max_part_segs * *np * sizeof(uint64_t) <= kDirectMaskBytes;
 }
 
@@ -2262,6 +2276,12 @@ lbl_status run_swm(const lbl_abs *a, const uint8_t *O, uint32_t n_props, void *w
     // mask kernels
     uint32_t np = 0;
     if (takes_direct(sp, n_props, &np)) {
+        if (sp.row_tiles) {
+            void *spn = spans ? span_begin(s) : nullptr;
+            const lbl_status st = run_row_tiles(a, *sp.row_tiles, O, n_props, L, s);
+            if (spans && st == LBL_OK) span_end(spn, s, 1);
+            return st;
+        }
         if (n_props == 1) return run_swm_direct<1>(a, O, n_props, ws, L, s, spans);
         if (n_props == 2) return run_swm_direct<2>(a, O, n_props, ws, L, s, spans);
         return run_swm_direct<4>(a, O, n_props, ws, L, s, spans);
