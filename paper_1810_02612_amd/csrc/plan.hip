@@ -22,13 +22,16 @@
 // on the one before, whether that one changed anything.  The sweep after the
 // first that did not writes the outputs, the ones after it do nothing.
 //
-// 568,958 transitions, 2 states, 16 to 17 sweeps: 179 us per call, 256 when
-// every sweep relaxed every reached edge and the host waited for each group
-// of four.  A sweep is bound by its chain of loads (5 us where little
-// changes, 2.3 when nothing is left) and by atomics on shared vertices in the
-// middle of the search (up to 14 us); changed vertices as bits set by atomics
-// took up to 37 us there, reading an edge's fields one after the other 9.0
-// instead of 7.1 us on average.
+// 568,958 transitions, 2 states: 135 us per call in 5 sweeps of up to 16 looks
+// (k_plan_sweep), 140 with 8, 154 with 4 and 175 with one, in 16 sweeps; 256
+// when every sweep relaxed every reached edge and the host waited for each
+// group of four.  Bound by the chain of the path's hops: source distance,
+// target distance, atomic minimum, about 1 us each.  An atomic for every
+// candidate instead of the check against the target's distance, which may be
+// old: 360-460 us, as the sinks' atomics go one by one.  Changed vertices as
+// bits set by atomics took up to 37 us in one sweep.  Random graphs of 100,000
+// vertices and 1,000,000 edges, 2 states: 1.93 ms, 2.02 with groups of four;
+// their edges sorted by source 1.17 and 1.80 ms.
 #include <algorithm>
 
 #include "lbl_internal.h"
@@ -131,8 +134,17 @@ __device__ __forceinline__ void best_min(uint64_t *best, uint64_t to, uint64_t c
 // judged by the value read, which may be older and larger than the current
 // one (the vertex is then relaxed once more, to no effect), so nothing waits
 // for the atomic minimum.
+//
+// A vertex that comes nearer is relaxed onward in the next sweep, or in this
+// one: a lane looks at its edge's source up to most_looks times and relaxes the
+// edge again when another workgroup has brought the source nearer meanwhile.
+// What it misses the next sweep does (the source is marked for it), so looks
+// change the number of sweeps, not the result, and none waits for anything.
+// Looks cost about 1 us each where the sources of a wavefront's edges share a
+// few cache lines (edges stored by source vertex) and far more where they
+// don't: such wavefronts look once.
 template <int S>
-__global__ void __launch_bounds__(256) k_plan_sweep(PlanArgs p, uint64_t k)
+__global__ void __launch_bounds__(256) k_plan_sweep(PlanArgs p, uint64_t k, uint32_t most_looks)
 {
     __shared__ uint8_t moves[S << 8];
     const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
@@ -161,35 +173,49 @@ __global__ void __launch_bounds__(256) k_plan_sweep(PlanArgs p, uint64_t k)
     for (uint64_t e = i0; e < p.n_edges; e += step) {
         const uint32_t u = p.src[e], v = p.dst[e], c = p.cost[e], sigma = p.sigma[e];
         if (!edge_ok(p, u, v, c)) continue;
-        const uint8_t active = now[u];
+        bool go = now[u] != 0;
         uint32_t du[S];
 #pragma unroll
         for (int q = 0; q < S; ++q) du[q] = (uint32_t)(p.best[(uint64_t)u * p.n_states + min((uint32_t)q, p.n_states - 1)] >> 32);
-        if (!active) continue;
-        uint64_t cand[S], to[S], old[S];
+        const uint32_t looks = __ballot((uint64_t)(u - (uint32_t)__builtin_amdgcn_readfirstlane((int)u)) * p.n_states >= 128u) == 0 ? most_looks : 1u;
+        for (uint32_t r = 1;; ++r) {
+            if (go) {
+                uint64_t cand[S], to[S], old[S];
 #pragma unroll
-        for (int q = 0; q < S; ++q) {
-            const uint32_t q2 = (uint32_t)q < p.n_states ? moves[((uint32_t)q << p.n_props) | sigma] : p.n_states;
-            const uint64_t nd = (uint64_t)du[q] + c;
-            to[q] = (uint64_t)v * p.n_states + min(q2, p.n_states - 1);
-            // no product edge: the source is not reached, the monitor
-            // rejects, the cost cannot be represented, or it ends at the
-            // start, which keeps distance 0 and no predecessor
-            const bool edge = du[q] != kInf && q2 < p.n_states && nd < kInf && to[q] != p.start;
-            cand[q] = edge ? (nd << 32) | (e * p.n_states + q) : kNone;
-            old[q] = p.best[to[q]];
-        }
-        bool nearer = false;
+                for (int q = 0; q < S; ++q) {
+                    const uint32_t q2 = (uint32_t)q < p.n_states ? moves[((uint32_t)q << p.n_props) | sigma] : p.n_states;
+                    const uint64_t nd = (uint64_t)du[q] + c;
+                    to[q] = (uint64_t)v * p.n_states + min(q2, p.n_states - 1);
+                    // no product edge: the source is not reached, the monitor
+                    // rejects, the cost cannot be represented, or it ends at the
+                    // start, which keeps distance 0 and no predecessor
+                    const bool edge = du[q] != kInf && q2 < p.n_states && nd < kInf && to[q] != p.start;
+                    cand[q] = edge ? (nd << 32) | (e * p.n_states + q) : kNone;
+                    old[q] = p.best[to[q]];
+                }
+                bool nearer = false;
 #pragma unroll
-        for (int q = 0; q < S; ++q)
-            if (cand[q] < old[q]) {  // values only decrease: otherwise it cannot win
-                best_min(p.best, to[q], cand[q]);
-                // a smaller edge id at the same distance changes no neighbour
-                nearer = nearer || cand[q] >> 32 < old[q] >> 32;
+                for (int q = 0; q < S; ++q)
+                    if (cand[q] < old[q]) {  // values only decrease: otherwise it cannot win
+                        best_min(p.best, to[q], cand[q]);
+                        // a smaller edge id at the same distance changes no neighbour
+                        nearer = nearer || cand[q] >> 32 < old[q] >> 32;
+                    }
+                if (nearer) {
+                    changed = true;
+                    next[v] = 1;
+                }
             }
-        if (nearer) {
-            changed = true;
-            next[v] = 1;
+            if (r >= looks) break;
+            // the source again, as the other workgroups have left it by now
+            go = false;
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const uint32_t *d = reinterpret_cast<const uint32_t *>(p.best + (uint64_t)u * p.n_states + min((uint32_t)q, p.n_states - 1)) + 1;
+                const uint32_t n = __hip_atomic_load(d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                go = go || n < du[q];
+                du[q] = min(du[q], n);
+            }
         }
     }
     const uint64_t any = __ballot(changed);  // one atomic per wavefront that saw a change
@@ -276,10 +302,13 @@ extern "C" lbl_status lbl_product_shortest_paths(uint64_t n_vertices, uint64_t n
     bool done = false;
     uint32_t idle = 0;
     const dim3 grid(blocks_for(n_edges));
+    // a look reads n_states distances per edge; with more edges than the chip
+    // holds threads, later edges wait for the looks of earlier ones
+    const uint32_t looks = std::min(n_edges > (1u << 21) ? 8u : 16u, std::max(4u, 32u / n_states));
     const auto sweep = n_states <= 1 ? k_plan_sweep<1> : n_states <= 2 ? k_plan_sweep<2> : n_states <= 4 ? k_plan_sweep<4> : k_plan_sweep<8>;
     while (!done && known <= n) {
         if (launched < known + 1 + kAhead && launched < n + 2) {
-            hipLaunchKernelGGL(sweep, grid, dim3(256), 0, s, p, launched);
+            hipLaunchKernelGGL(sweep, grid, dim3(256), 0, s, p, launched, looks);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) {
                 (void)hipStreamSynchronize(s);  // the pinned memory and the caller's arrays are still in use
