@@ -69,6 +69,7 @@ struct lbl_server {
     std::mutex mu;
     std::condition_variable cv_work, cv_done;
     std::deque<Request> pending;
+    size_t planning = 0;  // requests taken from pending whose batch is being planned
     std::unordered_map<uint64_t, Outcome> tickets;
     uint64_t next_ticket = 1;
     std::vector<Slot> slots;
@@ -111,7 +112,6 @@ void finish_slot(lbl_server *S, Slot &sl, lbl_status st, const std::string &msg)
     S->cv_done.notify_all();
 }
 
-// Launch the requests in `take` on slot `sl` (lock held).
 // Whether a batch of this one request runs the one-frame kernels on slot sl
 // (the abstraction has the sparse layout and their workspace fits the arena).
 bool runs_alone(const Slot &sl, const Request &r)
@@ -120,8 +120,10 @@ bool runs_alone(const Slot &sl, const Request &r)
 }
 
 // Launch the requests in take on slot sl: plan is their batch plan, or null
-// for a single request that runs alone.
-void launch(lbl_server *S, Slot &sl, std::vector<Request> &take, const BatchPlan *plan)
+// for a single request that runs alone.  lk is held on entry and on return,
+// and released while the batch is laid out and enqueued (only the worker
+// touches a slot).
+void launch(lbl_server *S, std::unique_lock<std::mutex> &lk, Slot &sl, std::vector<Request> &take, const BatchPlan *plan)
 {
     S->batches++;
     sl.reqs.swap(take);
@@ -142,8 +144,10 @@ void launch(lbl_server *S, Slot &sl, std::vector<Request> &take, const BatchPlan
     // one-frame kernels, with the slot's arena as their workspace: no batch
     // tables to upload and one launch fewer (the labels are the same)
     if (alone) {
+        lk.unlock();
         lbl_status st = run_swm(j0.a, j0.O, j0.n_props, sl.arena, j0.L, sl.stream, false);
         hipError_t e = st == LBL_OK ? hipEventRecord(sl.done, sl.stream) : hipSuccess;
+        lk.lock();
         if (st != LBL_OK) finish_slot(S, sl, st, "frame launch failed");
         else if (e != hipSuccess) finish_slot(S, sl, LBL_EDEVICE, hipGetErrorString(e));
         return;
@@ -152,9 +156,11 @@ void launch(lbl_server *S, Slot &sl, std::vector<Request> &take, const BatchPlan
         finish_slot(S, sl, LBL_EINVAL, "batch launched without a plan");
         return;
     }
+    lk.unlock();
     BatchBuffers bufs;
     std::vector<uint8_t> img;
     if (bind_batch(*plan, sl.arena, sl.arena_bytes, &bufs, &img) != LBL_OK) {
+        lk.lock();
         finish_slot(S, sl, LBL_ENOMEM, "batch does not fit the slot's arena");
         return;
     }
@@ -181,19 +187,41 @@ void launch(lbl_server *S, Slot &sl, std::vector<Request> &take, const BatchPlan
         st = LBL_EDEVICE;
         err = hipGetErrorString(e);
     }
+    lk.lock();
     if (st != LBL_OK) finish_slot(S, sl, st, err);
 }
 
-// Bytes a batch of these requests needs (0 and *ok = false if the jobs are invalid).
-size_t batch_bytes(const std::vector<Request> &reqs, BatchPlan *plan, bool *ok)
+// Bytes a batch of the first n of these requests needs (0 and *ok = false if
+// the jobs are invalid).
+size_t batch_bytes(const std::vector<Request> &reqs, size_t n, BatchPlan *plan, bool *ok)
 {
     std::vector<JobRef> jobs;
-    jobs.reserve(reqs.size());
-    for (const Request &r : reqs) jobs.push_back(r.job);
+    jobs.reserve(n);
+    for (size_t i = 0; i < n; ++i) jobs.push_back(reqs[i].job);
     *ok = plan_batch(jobs.data(), jobs.size(), -1, plan) == LBL_OK;
     if (!*ok) return 0;
     plan_finalize(*plan, batch_tile_for(plan->shape_key));
     return plan->device_bytes();
+}
+
+// The most of these requests, from the first, that a batch of at most `bytes`
+// holds, and that batch's plan.  All of them nearly always: one plan, where
+// planning every prefix took most of the worker's time.
+size_t fit_batch(const std::vector<Request> &reqs, size_t bytes, BatchPlan *plan)
+{
+    size_t fits = 0, too_many = reqs.size() + 1;
+    for (size_t n = reqs.size(); n > fits; n = (fits + too_many) / 2) {
+        BatchPlan p;
+        bool ok = false;
+        const size_t need = batch_bytes(reqs, n, &p, &ok);
+        if (ok && need <= bytes) {
+            fits = n;
+            *plan = std::move(p);
+        } else {
+            too_many = n;
+        }
+    }
+    return fits;
 }
 
 void worker_main(lbl_server *S)
@@ -221,28 +249,27 @@ void worker_main(lbl_server *S)
             if (S->pending.size() == 1 && runs_alone(sl, S->pending.front())) {
                 take.push_back(S->pending.front());
                 S->pending.pop_front();
-                launch(S, sl, take, nullptr);
+                launch(S, lk, sl, take, nullptr);
                 any_busy = any_busy || sl.busy;
                 continue;
             }
             BatchPlan plan;
             while (!S->pending.empty() && take.size() < S->cfg.max_batch_frames) {
                 take.push_back(S->pending.front());
-                bool ok = false;
-                BatchPlan cand;
-                const size_t need = batch_bytes(take, &cand, &ok);
-                if (!ok || need > sl.arena_bytes) {
-                    take.pop_back();
-                    break;
-                }
-                plan = std::move(cand);
                 S->pending.pop_front();
             }
+            S->planning = take.size();
+            lk.unlock();  // clients go on submitting
+            const size_t fits = fit_batch(take, sl.arena_bytes, &plan);
+            lk.lock();
+            S->planning = 0;
+            S->pending.insert(S->pending.begin(), take.begin() + (ptrdiff_t)fits, take.end());
+            take.resize(fits);
             if (take.empty() && runs_alone(sl, S->pending.front())) {
                 // the head request fits no batch but runs alone
                 take.push_back(S->pending.front());
                 S->pending.pop_front();
-                launch(S, sl, take, nullptr);
+                launch(S, lk, sl, take, nullptr);
                 any_busy = any_busy || sl.busy;
                 continue;
             }
@@ -258,7 +285,7 @@ void worker_main(lbl_server *S)
                 S->cv_done.notify_all();
                 continue;
             }
-            launch(S, sl, take, &plan);
+            launch(S, lk, sl, take, &plan);
             any_busy = any_busy || sl.busy;
         }
         if (S->stopping && S->pending.empty() && !any_busy) {
@@ -347,7 +374,7 @@ lbl_status lbl_serve_submit(lbl_server_t S, lbl_abs_t a, const uint8_t *O, uint3
         if (!alone) {
             std::vector<Request> one{r};
             BatchPlan plan;
-            need = batch_bytes(one, &plan, &ok);
+            need = batch_bytes(one, 1, &plan, &ok);
         }
         std::lock_guard<std::mutex> lk(S->mu);
         if (S->stopping) {
@@ -359,7 +386,7 @@ lbl_status lbl_serve_submit(lbl_server_t S, lbl_abs_t a, const uint8_t *O, uint3
             set_error("request needs " + std::to_string(need) + " bytes, more than a slot's share of the HBM budget");
             return LBL_ENOMEM;
         }
-        if (S->pending.size() >= S->cfg.max_queue) {
+        if (S->pending.size() + S->planning >= S->cfg.max_queue) {
             S->rejected++;
             set_error("request queue is full");
             return LBL_EBUSY;
