@@ -244,11 +244,10 @@ lbl_status lbl_label_frame_noalloc(lbl_abs_t a, const uint8_t *O, uint32_t n_pro
  * further passes in the same launch).  Workgroups pull (abstraction, row
  * range) items from a queue, largest first.
  *
- * The whole pipeline of a batch (O packing, labeling, label bytes) is
- * recorded once as a HIP graph keyed by (hip_stream, jobs, launch choice)
- * and replayed when the same batch is submitted again on that stream; the
- * graph owns its tables and packed masks (up to 8 graphs are cached; the
- * oldest is released after a device synchronization).  Results are
+ * A batch (its tables on the device and room for its packed masks and partial
+ * labels) is laid out once for (hip_stream, jobs, launch choice) and kept for
+ * when the same batch is submitted again on that stream (up to 8 are kept;
+ * the oldest is released after a device synchronization).  Results are
  * identical to labeling each job alone.
  *
  * Jobs on one abstraction are placed into 64-column lane groups first-fit by
@@ -329,8 +328,8 @@ lbl_status lbl_tune(lbl_abs_t a, const uint8_t *O_sample, uint32_t n_props, uint
 /* Time the batch's launch choices on this batch and record the fastest for
  * its shape class (whether every abstraction has the sparse layout, and the
  * multiset of (words per row, lane groups) of its passes); later
- * lbl_label_batch calls of that class use it, and the graph cached for
- * these jobs is rebuilt if it was made for another choice.  Sparse batches:
+ * lbl_label_batch calls of that class use it, and the batch kept for
+ * these jobs is laid out again if it was made for another choice.  Sparse batches:
  * the tiling of the layout (the one-frame tiling, or 1, 2, 4, 8 tiles per row
  * block) and the launch (persistent workgroups pulling tiles from per-XCD
  * queues, or one workgroup per tile).  Bitpacked batches: rows per work
@@ -339,7 +338,7 @@ lbl_status lbl_tune(lbl_abs_t a, const uint8_t *O_sample, uint32_t n_props, uint
 lbl_status lbl_tune_batch(const lbl_job *jobs, size_t n_jobs, void *hip_stream);
 /* Describe into buf (NUL-terminated) the shape class of a batch and the
  * launch choice lbl_label_batch would use for it on hip_stream, followed by
- * "cached" if a graph for these jobs with that choice exists, else "not
+ * "cached" if a batch of these jobs with that choice is kept, else "not
  * built".  Host only; launches nothing. */
 lbl_status lbl_tune_batch_describe(const lbl_job *jobs, size_t n_jobs, void *hip_stream, char *buf, size_t buf_len);
 lbl_status lbl_tune_save(const char *path);

@@ -1,5 +1,5 @@
 // Batched labeling: many frames over several abstractions in one persistent
-// launch.  Used by lbl_label_batch (graph-cached) and by the server (direct).
+// launch.  Used by lbl_label_batch (plans kept) and by the server.
 #pragma once
 
 #include "lbl_internal.h"
@@ -98,13 +98,17 @@ struct WorkItem {
 // and rows_per_item; sparse plans use tiling (0: the plan's default; else
 // 1 + the index of the layout's tiling: 1 = the one-frame tiling, 2..5 = 1,
 // 2, 4, 8 tiles per row block) and persistent (1: one workgroup per CU
-// pulling tiles from per-XCD queues; 0: one workgroup per tile).
+// pulling tiles from per-XCD queues; 0: one workgroup per tile, costliest
+// first; -1: the plan's default, 0.  Us per batch, 1 and 0: six maps x 16
+// frames, 2 tiles per row block 540 and 543, 8 tiles 618 and 584; 25k rows x
+// 128^2 x 4 32 and 21; 100k x 256^2 x 2 50 and 30: the queues cost a kernel
+// that clears them and an atomic and two barriers per item).
 struct BatchTile {
     int unroll = 8;
     int waves_per_block = 4;
     int rows_per_item = 128;
     int tiling = 0;
-    int persistent = 1;
+    int persistent = -1;
     bool operator==(const BatchTile &o) const
     {
         return unroll == o.unroll && waves_per_block == o.waves_per_block && rows_per_item == o.rows_per_item &&

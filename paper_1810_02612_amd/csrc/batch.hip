@@ -6,8 +6,10 @@
 // every job is one kernel; the labeling is one persistent kernel whose
 // workgroups pull (group, row range) items from an atomic counter, largest
 // items first, so uneven abstractions share the GPU without a tail of idle
-// CUs.  lbl_label_batch records the whole pipeline once as a HIP graph keyed
-// by (stream, jobs, flags) and replays it.
+// CUs.  lbl_label_batch keeps a batch's plan and device tables by (stream,
+// jobs, flags) and launches its kernels again when the batch comes again (a
+// captured graph of them took 25 us of host time to replay, the three launches
+// 8: 25k rows x 128^2, 4 frames, 39 us per call against 32).
 #include <algorithm>
 #include <cstring>
 #include <list>
@@ -32,7 +34,7 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int src)
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Zero the work counter (a kernel, not a memset node, so graph replays are safe).
+// Zero the work counter (a kernel, not a memset: safe where the caller captures).
 __global__ void k_zero(uint32_t *counter) { *counter = 0u; }
 
 // Zero n counters (n <= 64).
@@ -265,15 +267,21 @@ lbl_status plan_batch(const JobRef *jobs, size_t n_jobs, int device, BatchPlan *
     std::sort(keys.begin(), keys.end());
     for (auto &s : keys) p.shape_key += s + ";";
     if (p.sparse) {
-        // default: the coarsest tiling (fewest partials) that still gives
-        // every CU about two tile workgroups
-        const uint64_t want = 2ull * (uint64_t)device_cu_count();
+        // default: the coarsest tiling (fewest partials) whose largest item is
+        // at most 1 / 1.6 of a CU's share of the work, else the finest.  Us per
+        // batch at 1, 2, 4 and 8 tiles per row block (share / largest item at
+        // 1): six maps x 16 frames 593, 543, 546, 584 (1.4); x 5 263, 222, 203,
+        // 216 (0.5); x 1 216, 123, 76, 67 (0.15); 100k rows x 256^2 x 24 122,
+        // 123, 111, 112 (0.6); x 2 90, 54, 37, 30 (0.1)
+        double total = 0;
+        for (size_t g = 0; g < p.groups.size(); ++g) total += (double)p.groups[g].G64 * (double)(p.groups[g].max_entry + 1);
         p.default_tiling = kBatchTilings;
         for (int t = 1; t <= kBatchTilings; ++t) {
-            uint64_t n = 0;
+            double largest = 0;
             for (size_t g = 0; g < p.groups.size(); ++g)
-                n += (uint64_t)p.groups[g].G64 * p.group_abs[g]->sp->tilings[t].n_tiles;
-            if (n >= want) {
+                largest = std::max(largest, (double)(p.groups[g].max_entry + 1) /
+                                                (double)std::max(1u, p.group_abs[g]->sp->tilings[t].n_tiles));
+            if (total / device_cu_count() >= 1.6 * largest) {
                 p.default_tiling = t;
                 break;
             }
@@ -308,6 +316,7 @@ void plan_finalize(BatchPlan &p, const BatchTile &tile)
     std::vector<uint32_t> idx(p.groups.size());
     for (uint32_t i = 0; i < idx.size(); ++i) idx[i] = i;
     if (p.sparse) {
+        if (p.tile.persistent < 0) p.tile.persistent = 0;
         p.tiling = tile.tiling >= 1 && tile.tiling <= kBatchTilings + 1 ? tile.tiling - 1 : p.default_tiling;
         for (size_t g = 0; g < p.groups.size(); ++g) {
             GroupDesc &d = p.groups[g];
@@ -493,7 +502,7 @@ lbl_status enqueue_batch(const BatchPlan &p, const BatchBuffers &b, hipStream_t 
     const uint64_t pack_blocks = std::max<uint64_t>(1, std::min<uint64_t>((p.pack_units + 3) / 4, 1u << 16));
     if (p.sparse) {
         if (p.tile.persistent) {
-            // queue counters start at zero (a kernel, so graph replays are safe)
+            // queue counters start at zero (a kernel, not a memset: safe where the caller captures)
             hipLaunchKernelGGL(k_zero_n, dim3(1), dim3(64), 0, s, b.d_queues, kXcds);
             LBL_HIP_TRY(hipGetLastError());
         }
@@ -541,9 +550,9 @@ BatchTile tuned_tile(const std::string &key)
     return it == g_tiles.end() ? BatchTile{} : it->second;
 }
 
-// ---------------------------------------------------------------- graph cache
+// ---------------------------------------------------------------- planned batches
 
-struct GraphEntry {
+struct BatchEntry {
     hipStream_t stream = nullptr;
     uint32_t flags = 0;
     std::vector<JobRef> jobs;
@@ -551,14 +560,12 @@ struct GraphEntry {
     BatchTile asked;  // the tile the entry was built for (before defaults were resolved)
     BatchBuffers bufs;
     void *dmem = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
     int device = 0;
 };
 
-std::mutex g_graph_mu;
-std::list<std::unique_ptr<GraphEntry>> g_graphs;  // most recent first
-const size_t kMaxGraphs = 8;
+std::mutex g_entry_mu;
+std::list<std::unique_ptr<BatchEntry>> g_entries;  // most recent first
+const size_t kMaxEntries = 8;
 
 bool same_jobs(const std::vector<JobRef> &a, const JobRef *b, size_t n)
 {
@@ -568,19 +575,17 @@ bool same_jobs(const std::vector<JobRef> &a, const JobRef *b, size_t n)
     return true;
 }
 
-void destroy_entry(GraphEntry *e)
+void destroy_entry(BatchEntry *e)
 {
     int cur = 0;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(e->device);
     (void)hipDeviceSynchronize();
-    if (e->exec) (void)hipGraphExecDestroy(e->exec);
-    if (e->graph) (void)hipGraphDestroy(e->graph);
     if (e->dmem) (void)hipFree(e->dmem);
     (void)hipSetDevice(cur);
 }
 
-lbl_status build_entry(GraphEntry *e)
+lbl_status build_entry(BatchEntry *e)
 {
     const size_t bytes = e->plan.device_bytes();
     LBL_HIP_TRY(hipMalloc(&e->dmem, bytes));
@@ -588,44 +593,29 @@ lbl_status build_entry(GraphEntry *e)
     lbl_status bst = bind_batch(e->plan, static_cast<uint8_t *>(e->dmem), bytes, &e->bufs, &img);
     if (bst != LBL_OK) return bst;
     LBL_HIP_TRY(hipMemcpy(e->dmem, img.data(), img.size(), hipMemcpyHostToDevice));
-    hipStream_t cs = nullptr;
-    LBL_HIP_TRY(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-    hipError_t err = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    lbl_status st = LBL_OK;
-    if (err == hipSuccess) {
-        st = enqueue_batch(e->plan, e->bufs, cs);
-        hipGraph_t g = nullptr;
-        hipError_t e2 = hipStreamEndCapture(cs, &g);
-        e->graph = g;
-        if (st == LBL_OK && e2 != hipSuccess) err = e2;
-    }
-    (void)hipStreamDestroy(cs);
-    if (st != LBL_OK) return st;
-    LBL_HIP_TRY(err);
-    LBL_HIP_TRY(hipGraphInstantiate(&e->exec, e->graph, nullptr, nullptr, 0));
     return LBL_OK;
 }
 
-// The cached graph for these jobs built for tile `want` (or for the tile
+// The entry kept for these jobs, built for tile `want` (or for the tile
 // recorded for their shape class when want is null), moved to the front;
 // null if none.  Lock held.  Entries for the same jobs built for another
 // tile are released.
-GraphEntry *find_entry(const JobRef *jobs, size_t n_jobs, uint32_t flags, hipStream_t s, int device,
+BatchEntry *find_entry(const JobRef *jobs, size_t n_jobs, uint32_t flags, hipStream_t s, int device,
                        const BatchTile *want)
 {
-    GraphEntry *hit = nullptr;
-    for (auto it = g_graphs.begin(); it != g_graphs.end();) {
-        GraphEntry *e = it->get();
+    BatchEntry *hit = nullptr;
+    for (auto it = g_entries.begin(); it != g_entries.end();) {
+        BatchEntry *e = it->get();
         if (e->stream == s && e->flags == flags && e->device == device && same_jobs(e->jobs, jobs, n_jobs)) {
             const BatchTile w = want ? *want : tuned_tile(e->plan.shape_key);
             if (!hit && e->asked == w) {
                 hit = e;
-                g_graphs.splice(g_graphs.begin(), g_graphs, it++);
+                g_entries.splice(g_entries.begin(), g_entries, it++);
                 continue;
             }
             if (!want) {  // built for a tile no longer recorded for the class
                 destroy_entry(e);
-                it = g_graphs.erase(it);
+                it = g_entries.erase(it);
                 continue;
             }
         }
@@ -646,13 +636,13 @@ std::vector<std::pair<std::string, BatchTile>> batch_tiles()
 
 void batch_forget(const lbl_abs *a)
 {
-    std::lock_guard<std::mutex> lk(g_graph_mu);
-    for (auto it = g_graphs.begin(); it != g_graphs.end();) {
+    std::lock_guard<std::mutex> lk(g_entry_mu);
+    for (auto it = g_entries.begin(); it != g_entries.end();) {
         bool uses = false;
         for (const JobRef &j : (*it)->jobs) uses = uses || j.a == a;
         if (uses) {
             destroy_entry(it->get());
-            it = g_graphs.erase(it);
+            it = g_entries.erase(it);
         } else {
             ++it;
         }
@@ -665,14 +655,14 @@ void set_batch_tile(const std::string &key, const BatchTile &t)
     g_tiles[key] = t;
 }
 
-lbl_status label_batch_graph(const JobRef *jobs, size_t n_jobs, uint32_t flags, hipStream_t s, const BatchTile *force)
+lbl_status label_batch_cached(const JobRef *jobs, size_t n_jobs, uint32_t flags, hipStream_t s, const BatchTile *force)
 {
     int cur = 0;
     LBL_HIP_TRY(hipGetDevice(&cur));
-    std::lock_guard<std::mutex> lk(g_graph_mu);
-    GraphEntry *hit = find_entry(jobs, n_jobs, flags, s, cur, force);
+    std::lock_guard<std::mutex> lk(g_entry_mu);
+    BatchEntry *hit = find_entry(jobs, n_jobs, flags, s, cur, force);
     if (!hit) {
-        std::unique_ptr<GraphEntry> e(new GraphEntry());
+        std::unique_ptr<BatchEntry> e(new BatchEntry());
         e->stream = s;
         e->flags = flags;
         e->device = cur;
@@ -686,15 +676,16 @@ lbl_status label_batch_graph(const JobRef *jobs, size_t n_jobs, uint32_t flags, 
             destroy_entry(e.get());
             return st;
         }
-        while (g_graphs.size() >= kMaxGraphs) {
-            destroy_entry(g_graphs.back().get());
-            g_graphs.pop_back();
+        while (g_entries.size() >= kMaxEntries) {
+            destroy_entry(g_entries.back().get());
+            g_entries.pop_back();
         }
-        g_graphs.push_front(std::move(e));
-        hit = g_graphs.front().get();
+        g_entries.push_front(std::move(e));
+        hit = g_entries.front().get();
     }
     void *span = span_begin(s);
-    LBL_HIP_TRY(hipGraphLaunch(hit->exec, s));
+    const lbl_status st = enqueue_batch(hit->plan, hit->bufs, s);
+    if (st != LBL_OK) return st;
     span_end(span, s, 2);
     return LBL_OK;
 }
@@ -712,7 +703,7 @@ lbl_status lbl_label_batch(const lbl_job *jobs, size_t n_jobs, uint32_t flags, v
     LBL_REQUIRE(flags == 0, "lbl_label_batch takes device pointers and no flags");
     std::vector<JobRef> refs(n_jobs);
     for (size_t j = 0; j < n_jobs; ++j) refs[j] = JobRef{jobs[j].a, jobs[j].O, jobs[j].n_props, jobs[j].L};
-    return label_batch_graph(refs.data(), n_jobs, flags, reinterpret_cast<hipStream_t>(hip_stream), nullptr);
+    return label_batch_cached(refs.data(), n_jobs, flags, reinterpret_cast<hipStream_t>(hip_stream), nullptr);
 }
 
 lbl_status lbl_tune_batch(const lbl_job *jobs, size_t n_jobs, void *hip_stream)
@@ -744,19 +735,19 @@ lbl_status lbl_tune_batch(const lbl_job *jobs, size_t n_jobs, void *hip_stream)
             for (int w : {4, 8, 16})
                 for (int r : {32, 128, 512}) cands.push_back(BatchTile{u, w, r, 0, 1});
     }
-    // each candidate: its graph built and replayed once, then `reps` replays
+    // each candidate: built and run once, then `reps` runs
     // timed one by one; its score is their median.  The candidates run within
     // a few percent of each other, so the three best are timed again with
-    // more replays and the lowest median wins.
+    // more runs and the lowest median wins.
     const int kEvents = 16;
     hipEvent_t ev[kEvents + 1];
     for (int i = 0; i <= kEvents; ++i) LBL_HIP_TRY(hipEventCreate(&ev[i]));
     auto score = [&](const BatchTile &t, int reps, float *out) -> lbl_status {
-        lbl_status r = label_batch_graph(refs.data(), n_jobs, 0, s, &t);  // build + warm-up
+        lbl_status r = label_batch_cached(refs.data(), n_jobs, 0, s, &t);  // build + warm-up
         if (r != LBL_OK) return r;
         LBL_HIP_TRY(hipEventRecord(ev[0], s));
         for (int k = 0; k < reps && r == LBL_OK; ++k) {
-            r = label_batch_graph(refs.data(), n_jobs, 0, s, &t);
+            r = label_batch_cached(refs.data(), n_jobs, 0, s, &t);
             LBL_HIP_TRY(hipEventRecord(ev[k + 1], s));
         }
         LBL_HIP_TRY(hipEventSynchronize(ev[reps]));
@@ -789,9 +780,9 @@ lbl_status lbl_tune_batch(const lbl_job *jobs, size_t n_jobs, void *hip_stream)
     for (int i = 0; i <= kEvents; ++i) (void)hipEventDestroy(ev[i]);
     if (st != LBL_OK) return st;
     set_batch_tile(probe.shape_key, best);
-    // release the candidates' graphs except the winner's, which the next
-    // lbl_label_batch of these jobs replays
-    std::lock_guard<std::mutex> lk(g_graph_mu);
+    // release the candidates' entries except the winner's, which the next
+    // lbl_label_batch of these jobs launches
+    std::lock_guard<std::mutex> lk(g_entry_mu);
     (void)find_entry(refs.data(), n_jobs, 0, s, cur, nullptr);
     return LBL_OK;
 }
@@ -810,10 +801,10 @@ lbl_status lbl_tune_batch_describe(const lbl_job *jobs, size_t n_jobs, void *hip
     if (st != LBL_OK) return st;
     std::string out;
     {
-        std::lock_guard<std::mutex> lk(g_graph_mu);
+        std::lock_guard<std::mutex> lk(g_entry_mu);
         hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-        GraphEntry *e = nullptr;
-        for (auto &x : g_graphs)
+        BatchEntry *e = nullptr;
+        for (auto &x : g_entries)
             if (x->stream == s && x->device == cur && same_jobs(x->jobs, refs.data(), n_jobs) &&
                 x->asked == tuned_tile(x->plan.shape_key)) {
                 e = x.get();
