@@ -1096,51 +1096,97 @@ k_label_tiles_queue(const GroupDesc *__restrict__ groups, const TileItem *__rest
     }
 }
 
-// Bit p set iff byte mis + p of the dwords p[0 ..] is non-zero, for p < n
-// (1 <= n <= 64, mis < 4).  Reads p[0 .. (n + 6) / 4] whatever mis is (the
-// caller's array extends that far); dwords past the range are dropped.
-__device__ __forceinline__ uint64_t byte_mask_words(const uint32_t *p, uint32_t mis, uint32_t n)
-{
-    const uint32_t nd = (mis + n + 3) >> 2;  // this lane's words: 1 .. 17
-    const uint32_t kmax = (n + 6) >> 2;      // an upper bound of nd for every lane
-    uint64_t lo = 0;
-#pragma unroll
-    for (uint32_t k = 0; k < 16; ++k)
-        if (k < kmax) {  // uniform
-            // dwords past this lane's range are dropped by a mask, not a branch
-            const uint32_t keep = 0u - (uint32_t)(k < nd);
-            lo |= (uint64_t)(nz_bytes(p[k]) & keep) << (4 * k);
-        }
-    const uint32_t hi = kmax > 16 ? nz_bytes(p[16]) & (0u - (uint32_t)(nd > 16)) : 0u;
-    const uint64_t m = mis ? (lo >> mis) | ((uint64_t)hi << (64 - mis)) : lo;
-    return n >= 64 ? m : m & ((1ull << n) - 1ull);
-}
-
-// LDS words a pack wavefront stages one job's bytes of one word in: 8 runs
-// of 8 cells (or one of 64) of at most 64 bytes, each from a dword boundary,
-// plus the dwords byte_mask_words may read past the last run.
-constexpr uint32_t kPackStaged = 8 * ((3 + 8 * 64 + 3) / 4);
-static_assert(kPackStaged >= (3 + 64 * 64 + 3) / 4, "a 64-cell run must fit the stage");
-constexpr uint32_t kPackStageWords = kPackStaged + 4;
-// Dword loads per lane in flight while a stage is filled.
-constexpr uint32_t kPackLoads = 9;
-
 typedef __attribute__((address_space(1))) const uint32_t global_u32;
 typedef __attribute__((address_space(1))) const uint64_t global_u64;
 
+// Words a pack wavefront takes at a time, and the most 16-byte units a lane
+// loads of one: 8 runs of 8 cells (or one of 64) of at most 64 bytes at any
+// address, 33 units to a run.
+constexpr uint32_t kPackWords = 2;
+constexpr uint32_t kPackUnits = 5;
+static_assert(kPackUnits * 64 >= 8 * ((15 + 8 * 64 + 15) / 16), "a word's units");
+constexpr uint32_t kPackStage = kPackUnits * 64 * 2 / 4 + 2;  // LDS dwords of a word: 16 bits per unit, two more read
+
+// What a pack lane knows of its cell in a word's 8 x 8 block: the run of
+// consecutive cells it lies in and its place there.
+struct PackLane {
+    uint32_t lane, run, pos, n_run, run_cells;
+};
+
+// Masks of kPackWords words for one job: m[k] gets the bits of this lane's cell
+// of the word whose first cell is cell[k].  The wavefront reads the words'
+// bytes in aligned 16-byte units, consecutive lanes consecutive units (a load
+// instruction touches 16 cache lines, where records read by the lanes that
+// need them touch one each), forms each unit's 16 bits, and lines them up in
+// LDS, where each lane's n_props bits are then one bit field.  A unit holds at
+// least one byte of its run (the last is read again past a run's end), so no
+// load leaves the pages the frame lies on.
+template <uint32_t K>
+__device__ __forceinline__ void pack_words(const SegDesc &d, const uint64_t (&cell)[kPackWords], uint32_t run_units,
+                                           uint32_t run_stride, const PackLane &l, uint32_t *stage, uint64_t (&m)[kPackWords])
+{
+    const uint32_t np = d.n_props, run_bytes = l.run_cells * np;
+    // floor(q / run_units) as umulhi(q, magic): exact for q * run_units < 2^32
+    const uint32_t magic = 0xFFFFFFFFu / run_units + 1u, last = l.n_run * run_units - 1;
+    global_u8 *base[kPackWords];
+    uint32_t mis[kPackWords];
+    v4u32 q[kPackWords][K];
+#pragma unroll
+    for (uint32_t w = 0; w < kPackWords; ++w) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(d.O) + cell[w] * np;
+        mis[w] = (uint32_t)(a & 15u);
+        base[w] = reinterpret_cast<global_u8 *>(a - mis[w]);
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < K; ++k) {
+        const uint32_t u = min(l.lane + 64 * k, last);
+        const uint32_t r = __umulhi(u, magic), j = u - r * run_units;
+        // byte offsets fit 32 bits: 7 runs of nx * np bytes (nx * ny < 2^31
+        // cells, np <= 64) plus one run
+        const uint32_t run0 = r * run_stride;
+#pragma unroll
+        for (uint32_t w = 0; w < kPackWords; ++w) {
+            const uint32_t at = mis[w] + run0;  // the run's first byte, from base
+            q[w][k] = *reinterpret_cast<__attribute__((address_space(1))) const v4u32 *>(
+                base[w] + min((at & ~15u) + 16 * j, (at + run_bytes - 1) & ~15u));
+        }
+    }
+#pragma unroll
+    for (uint32_t w = 0; w < kPackWords; ++w) {
+        uint16_t *s16 = reinterpret_cast<uint16_t *>(stage + w * kPackStage);
+#pragma unroll
+        for (uint32_t k = 0; k < K; ++k)
+            s16[l.lane + 64 * k] = (uint16_t)nz_bytes16(q[w][k].x, q[w][k].y, q[w][k].z, q[w][k].w);
+    }
+    // LDS instructions of a wavefront complete in issue order; the barriers
+    // keep the compiler from moving the reads above the writes, or the next
+    // job's writes above these reads
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (uint32_t w = 0; w < kPackWords; ++w) {
+        const uint32_t o = 16 * l.run * run_units + ((mis[w] + l.run * run_stride) & 15u) + l.pos * np;
+        const uint32_t *f = stage + w * kPackStage + (o >> 5);
+        const uint32_t lo = __builtin_amdgcn_alignbit(f[1], f[0], o & 31u), hi = __builtin_amdgcn_alignbit(f[2], f[1], o & 31u);
+        const uint64_t v = (uint64_t)hi << 32 | lo;
+        m[w] |= (np >= 64 ? v : v & ((1ull << np) - 1ull)) << d.bit;
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
 // One wavefront per pack item (pass, lane group, words [w0, w1)): for each
 // word, lane b builds the proposition mask of the word's cell b over the
-// lane group's columns, then the word's nibble tables for the lane group are
-// written.  A job's bytes of the word's 64 cells are n_props-byte records in
-// 8 runs of 8 consecutive cells (row-major ids: one run per cell row of the
-// 8 x 8 tile, nx cells apart) or one run of 64 (z-order ids); they are
-// staged in LDS with coalesced dword loads (every run starts at the same
-// offset within a dword, since cell ids of a run start are multiples of 8),
-// and each lane then reads its cell's record from LDS.
+// lane group's columns (pack_words), then the word's nibble tables (or its
+// cell masks, for a layout in run entries) for the lane group are written.
+//
+// Six maps x 16 frames (374 MB of frames, 34 propositions on average): 107 us,
+// 526 MB fetched (a run's ends share lines with its neighbours').
+// Staging the bytes in LDS by coalesced dwords and forming the bits of each
+// record afterwards: 118 us, two vector instructions per byte; each lane
+// loading its own cell's bytes: 116, a cache access per lane and load.
 __global__ void __launch_bounds__(256)
 k_pack_batch_tables(const GroupDesc *__restrict__ groups, const PackItem *__restrict__ items, uint32_t n_items)
 {
-    __shared__ uint32_t stage_all[4][kPackStageWords];
+    __shared__ uint32_t stage_all[4][kPackWords * kPackStage];
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t i = blockIdx.x * 4 + wv;
@@ -1148,11 +1194,8 @@ k_pack_batch_tables(const GroupDesc *__restrict__ groups, const PackItem *__rest
     uint32_t *stage = stage_all[wv];
     const PackItem it = items[i];
     const GroupDesc &g = groups[it.group];
-    // values read through pointers held in the descriptors come back in
-    // vector registers; they are wavefront-uniform, and are moved to scalar
-    // registers so that the loops and offsets derived from them are scalar
-    auto uni = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
-    const uint32_t s0 = uni(g.lg_seg[it.gi]), s1 = uni(g.lg_seg[it.gi + 1]);
+    const uint32_t s0 = __builtin_amdgcn_readfirstlane((int)g.lg_seg[it.gi]);
+    const uint32_t s1 = __builtin_amdgcn_readfirstlane((int)g.lg_seg[it.gi + 1]);
     const bool zo = g.morton != 0;
     // lane b is the cell at (dx, dy) of the word's 8 x 8 tile, x taking the
     // odd bits of b; in z-order ids it is the word's cell b
@@ -1160,61 +1203,36 @@ k_pack_batch_tables(const GroupDesc *__restrict__ groups, const PackItem *__rest
     const bool rows = g.sp_ent != nullptr;
     const uint32_t dx = rows ? lane & 7u : ((lane >> 1) & 1u) | ((lane >> 2) & 2u) | ((lane >> 3) & 4u);
     const uint32_t dy = rows ? lane >> 3 : (lane & 1u) | ((lane >> 1) & 2u) | ((lane >> 2) & 4u);
-    const uint32_t n_run = zo ? 1u : 8u, run_cells = zo ? 64u : 8u;
-    const uint32_t my_run = zo ? 0u : dy, my_pos = zo ? (rows ? word_z(dx, dy) : lane) : dx;
+    const PackLane l{lane, zo ? 0u : dy, zo ? (rows ? word_z(dx, dy) : lane) : dx, zo ? 1u : 8u, zo ? 64u : 8u};
     const global_u32 *word_cell = (const global_u32 *)g.word_cell;
-    for (uint32_t w = it.w0; w < it.w1; ++w) {
-        // the word's first cell (dx = dy = 0), wavefront-uniform (read into
-        // a scalar register, so that everything derived from it is scalar)
-        const uint32_t c0 = zo ? w * 64 : word_cell[(uint64_t)w * 64];
-        const uint64_t cell0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)c0);
-        uint64_t m = 0;
-        for (uint32_t sgi = s0; sgi < s1; ++sgi) {
-            const SegDesc d = g.segs[sgi];
-            const uint32_t np = uni(d.n_props), bit = uni(d.bit);
-            const uintptr_t o_addr = ((uintptr_t)uni((uint32_t)((uintptr_t)d.O >> 32)) << 32) | uni((uint32_t)(uintptr_t)d.O);
-            const uintptr_t a0 = o_addr + cell0 * np;
-            const uint32_t mis = (uint32_t)(a0 & 3u);
-            const uint32_t nd = (mis + run_cells * np + 3) >> 2;  // dwords per run, >= 2
-            // byte offsets from base fit 32 bits: 7 runs of nx * np bytes
-            // (nx * ny < 2^31 cells, np <= 64) plus one run's dwords
-            const uint32_t run_stride = zo ? 0u : g.nx * np;
-            const __attribute__((address_space(1))) uint8_t *base =
-                reinterpret_cast<const __attribute__((address_space(1))) uint8_t *>(a0 - mis);
-            // floor(q / nd) as umulhi(q, magic): exact for q * nd < 2^32
-            const uint32_t magic = 0xFFFFFFFFu / nd + 1u;
-            const uint32_t total = n_run * nd;  // <= kPackStageWords
-            // the loads of a phase (up to kPackLoads per lane) are all issued
-            // before the first is stored, so the wavefront waits for memory
-            // once per phase: once per job and word up to 35 propositions
-            // (8 runs of at most 72 dwords), twice above
-            // Lanes past the end take the last dword again (loaded and
-            // stored twice with the same value), so no lane branches.
-            for (uint32_t q0 = 0; q0 < total; q0 += 64 * kPackLoads) {
-                uint32_t v[kPackLoads], at[kPackLoads];
+    for (uint32_t w0 = it.w0; w0 < it.w1; w0 += kPackWords) {
+        uint64_t m[kPackWords] = {}, cell[kPackWords];
 #pragma unroll
-                for (uint32_t k = 0; k < kPackLoads; ++k)
-                    if (q0 + 64 * k < total) {  // uniform
-                        const uint32_t q = min(q0 + lane + 64 * k, total - 1);
-                        const uint32_t r = __umulhi(q, magic), j = q - r * nd;
-                        at[k] = q;
-                        v[k] = *reinterpret_cast<const global_u32 *>(base + (r * run_stride + 4u * j));
-                    }
-#pragma unroll
-                for (uint32_t k = 0; k < kPackLoads; ++k)
-                    if (q0 + 64 * k < total) stage[at[k]] = v[k];
-            }
-            // LDS instructions of a wavefront complete in issue order; the
-            // barrier keeps the compiler from moving the reads above the writes
-            __builtin_amdgcn_wave_barrier();
-            const uint32_t off = my_run * nd * 4 + mis + my_pos * np;
-            m |= byte_mask_words(stage + (off >> 2), off & 3u, np) << bit;
-            __builtin_amdgcn_wave_barrier();  // the next job overwrites the stage
+        for (uint32_t k = 0; k < kPackWords; ++k) {
+            // past the last word that one again, which is not stored
+            const uint32_t w = min(w0 + k, it.w1 - 1);
+            cell[k] = zo ? (uint64_t)w * 64 : (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)word_cell[(uint64_t)w * 64]);
         }
-        if (rows)
-            g.Ow[((uint64_t)w * g.G64 + it.gi) * 64 + lane] = m;
-        else
-            write_tables(m, g.Ow + ((uint64_t)w * g.G64 + it.gi) * 256, lane);
+        for (uint32_t sgi = s0; sgi < s1; ++sgi) {
+            const SegDesc d = uniform_seg(g.segs, sgi);
+            const uint32_t units = (15 + l.run_cells * d.n_props + 15) >> 4, stride = zo ? 0u : g.nx * d.n_props;
+            switch ((l.n_run * units + 63) / 64) {  // uniform
+            case 1: pack_words<1>(d, cell, units, stride, l, stage, m); break;
+            case 2: pack_words<2>(d, cell, units, stride, l, stage, m); break;
+            case 3: pack_words<3>(d, cell, units, stride, l, stage, m); break;
+            case 4: pack_words<4>(d, cell, units, stride, l, stage, m); break;
+            default: pack_words<5>(d, cell, units, stride, l, stage, m); break;
+            }
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kPackWords; ++k)
+            if (w0 + k < it.w1) {
+                const uint64_t at = (uint64_t)(w0 + k) * g.G64 + it.gi;
+                if (rows)
+                    g.Ow[at * 64 + lane] = m[k];
+                else
+                    write_tables(m[k], g.Ow + at * 256, lane);
+            }
     }
 }
 

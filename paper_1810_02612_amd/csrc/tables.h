@@ -7,82 +7,82 @@
 
 namespace lbl {
 
-// Nonzero bytes of a 32-bit word -> 4 bits (bit k for byte k).
-__device__ __forceinline__ uint32_t nz_bytes(uint32_t x)
+// High bit of each byte of x: the byte is not zero.
+__device__ __forceinline__ uint32_t nz_high(uint32_t x) { return (((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u; }
+
+// Nonzero bytes of a 32-bit word -> 4 bits (bit k for byte k): the bytes'
+// flags (0 or 128) weighted 1, 2, 4, 8 and summed in one instruction.
+__device__ __forceinline__ uint32_t nz_bytes(uint32_t x) { return __builtin_amdgcn_udot4(nz_high(x), 0x08040201u, 0u, false) >> 7; }
+
+// Nonzero bytes of 8 bytes -> 8 bits.
+__device__ __forceinline__ uint32_t nz_bytes8(uint32_t x, uint32_t y)
 {
-    const uint32_t y = ((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x;  // high bit of each byte: byte != 0
-    const uint32_t h = y & 0x80808080u;
-    return ((h >> 7) | (h >> 14) | (h >> 21) | (h >> 28)) & 0xFu;
+    return __builtin_amdgcn_udot4(nz_high(y), 0x80402010u, __builtin_amdgcn_udot4(nz_high(x), 0x08040201u, 0u, false), false) >> 7;
 }
 
 // Four bits -> four bytes 0/1 (bit k to byte k).
 __device__ __forceinline__ uint32_t spread_nib(uint32_t x) { return (x * 0x00204081u) & 0x01010101u; }
 
 // Nonzero bytes of 16 bytes -> 16 bits (bit k for byte k).
-__device__ __forceinline__ uint32_t nz_bytes16(const uint4 &q)
+__device__ __forceinline__ uint32_t nz_bytes16(uint32_t x, uint32_t y, uint32_t z, uint32_t w)
 {
-    return nz_bytes(q.x) | (nz_bytes(q.y) << 4) | (nz_bytes(q.z) << 8) | (nz_bytes(q.w) << 12);
+    return nz_bytes8(x, y) | (nz_bytes8(z, w) << 8);
+}
+__device__ __forceinline__ uint32_t nz_bytes16(const uint4 &q) { return nz_bytes16(q.x, q.y, q.z, q.w); }
+
+// Loads from any byte address of device memory.
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
+typedef __attribute__((address_space(1))) const uint8_t global_u8;
+template <typename T>
+__device__ __forceinline__ T load_any(global_u8 *p)
+{
+    return *reinterpret_cast<__attribute__((address_space(1))) const T *>(p);
 }
 
-// Bit p set iff byte p of src[0 .. n) is non-zero, 1 <= n <= 64; 16-, 4- or
-// 2-byte loads when n and the address allow.  A group of four loads is
-// issued before the first of its results is used (a loop that used each load
-// before issuing the next would wait out the memory latency once per load):
-// indices past the last piece repeat the last load, which stays in bounds,
-// and their bits are dropped by a select rather than a branch, which the
-// compiler would turn into a load under a branch again.
-__device__ __forceinline__ uint64_t byte_mask(const uint8_t *src, uint32_t n)
+// byte_mask of 16 C - 15 .. 16 C bytes.
+template <uint32_t C>
+__device__ __forceinline__ uint64_t byte_mask_16(global_u8 *src, uint32_t n)
 {
+    u32x4_any q[C];
+#pragma unroll
+    for (uint32_t k = 0; k < C; ++k) q[k] = load_any<u32x4_any>(src + (k + 1 < C ? 16 * k : n - 16));
     uint64_t m = 0;
-    const uintptr_t a = reinterpret_cast<uintptr_t>(src);
-    if ((n & 15u) == 0 && (a & 15u) == 0) {
-        const uint32_t last = n / 16 - 1;  // at most 3
-        uint4 q[4];
 #pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) q[k] = reinterpret_cast<const uint4 *>(src)[min(k, last)];
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) {
-            const uint64_t b = (uint64_t)nz_bytes16(q[k]) << (16 * k);
-            m |= k <= last ? b : 0ull;
-        }
-    } else if ((n & 3u) == 0 && (a & 3u) == 0) {
-        const uint32_t last = n / 4 - 1;  // at most 15
-        for (uint32_t k0 = 0; k0 <= last; k0 += 4) {
-            uint32_t d[4];
-#pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) d[k] = reinterpret_cast<const uint32_t *>(src)[min(k0 + k, last)];
-#pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) {
-                const uint64_t b = (uint64_t)nz_bytes(d[k]) << ((4 * (k0 + k)) & 63u);
-                m |= k0 + k <= last ? b : 0ull;
-            }
-        }
-    } else if ((n & 1u) == 0 && (a & 1u) == 0) {
-        const uint32_t last = n / 2 - 1;  // at most 31
-        for (uint32_t k0 = 0; k0 <= last; k0 += 4) {
-            uint32_t h[4];
-#pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) h[k] = reinterpret_cast<const uint16_t *>(src)[min(k0 + k, last)];
-#pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) {
-                const uint32_t two = ((h[k] & 0xFFu) != 0 ? 1u : 0u) | ((h[k] >> 8) != 0 ? 2u : 0u);
-                const uint64_t b = (uint64_t)two << ((2 * (k0 + k)) & 63u);
-                m |= k0 + k <= last ? b : 0ull;
-            }
-        }
-    } else {
-        for (uint32_t p0 = 0; p0 < n; p0 += 4) {
-            uint32_t c[4];
-#pragma unroll
-            for (uint32_t j = 0; j < 4; ++j) c[j] = src[min(p0 + j, n - 1)];
-#pragma unroll
-            for (uint32_t j = 0; j < 4; ++j) {
-                const uint64_t b = (uint64_t)(c[j] != 0 ? 1u : 0u) << ((p0 + j) & 63u);
-                m |= p0 + j < n ? b : 0ull;
-            }
-        }
-    }
+    for (uint32_t k = 0; k < C; ++k)
+        m |= (uint64_t)nz_bytes16(q[k].x, q[k].y, q[k].z, q[k].w) << (k + 1 < C ? 16 * k : n - 16);
     return m;
+}
+
+// Bit p set iff byte p of bytes[0 .. n) (device memory, any address) is
+// non-zero, 1 <= n <= 64, n the same in every lane.  The bytes are read in
+// the widest pieces that fit, all of them before the first is used; the last
+// piece ends with the last byte and may read bytes of the one before again,
+// so no byte outside is read and no piece is narrower than it need be.  For
+// 37 bytes that is three 16-byte loads, where single bytes in groups of four
+// took ten waits for memory (packing 75,003 x 328 x 200 x 37: 5.6 -> 3.3 us).
+__device__ __forceinline__ uint64_t byte_mask(const uint8_t *bytes, uint32_t n)
+{
+    global_u8 *src = (global_u8 *)bytes;
+    if (n > 48) return byte_mask_16<4>(src, n);
+    if (n > 32) return byte_mask_16<3>(src, n);
+    if (n > 16) return byte_mask_16<2>(src, n);
+    if (n == 16) return byte_mask_16<1>(src, n);
+    if (n >= 8) {
+        const u32x2_any a = load_any<u32x2_any>(src), b = load_any<u32x2_any>(src + n - 8);
+        return nz_bytes8(a.x, a.y) | (nz_bytes8(b.x, b.y) << (n - 8));
+    }
+    if (n >= 4) {
+        const uint32_t a = load_any<u32_any>(src), b = load_any<u32_any>(src + n - 4);
+        return nz_bytes(a) | (nz_bytes(b) << (n - 4));
+    }
+    if (n >= 2) {
+        const uint32_t a = load_any<u16_any>(src), b = load_any<u16_any>(src + n - 2);
+        return nz_bytes(a) | (nz_bytes(b) << (n - 2));
+    }
+    return src[0] != 0;
 }
 
 // Value of lane C of each group of four lanes (DPP quad permutation).
