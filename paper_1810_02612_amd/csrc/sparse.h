@@ -62,7 +62,7 @@ struct SpTask {
 struct SpRound {
     uint32_t e_off;  // multiple of 64
     uint32_t tword;  // word whose tables the round copies (the last built word if none)
-    uint32_t pad;
+    uint32_t tcell;  // first cell id of tword (run layouts)
     uint32_t meta;   // lane_lo | lane_hi << 8 | cut << 16 | build0 << 24 | build1 << 25 | slot0 << 26
 };
 constexpr uint32_t kMetaBuild0 = 1u << 24, kMetaBuild1 = 1u << 25, kMetaSlot0 = 1u << 26;
@@ -241,6 +241,10 @@ void make_tiling(const std::vector<uint64_t> &seg_start, const std::vector<uint3
 void make_run_tiling(const std::vector<uint64_t> &start, const std::vector<uint32_t> &seg_word,
                      const std::vector<uint64_t> &rb_seg, const std::vector<uint32_t> &tiles_rb, TilingHost *out);
 std::vector<double> run_costs(const std::vector<uint64_t> &start, const std::vector<uint64_t> &rb_seg);
+// Whether one frame's tiles form their words' cell masks from O themselves,
+// instead of a pack kernel: each of n_seg segments reads its word's 64 cells of
+// n_props bytes again.  aligned: cells start at multiples of 4 bytes.
+bool tiles_pack(uint64_t n_seg, uint32_t n_props, bool aligned);
 // Whether a layout of nnz words that take n_ent run entries is labeled by the
 // run kernels.
 bool use_runs(uint64_t nnz, uint64_t n_ent);

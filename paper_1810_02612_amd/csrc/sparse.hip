@@ -37,7 +37,9 @@
 //                  the caller's L bytes (0/1).
 // Layouts in run entries (runs.h; use_runs) are labeled by the same three
 // steps with k_pack_cells, which writes the cells' masks, and k_label_runs,
-// whose wavefronts build the tables of 8-cell rows themselves.
+// whose wavefronts build the tables of 8-cell rows themselves; where there are
+// few segments (tiles_pack) k_label_runs_frame forms the masks from O as well,
+// and there is no pack kernel.
 // Frames of at most 4 propositions take two other kernels instead:
 //   k_pack_masks   O -> NP proposition masks per used word (bit b = cell b);
 //                  the grid also zeroes L.
@@ -638,8 +640,88 @@ __device__ __forceinline__ void tile_accumulate(const SpTask *__restrict__ wg_ta
     __syncthreads();
 }
 
-// tile_accumulate for a layout in run entries: Tm + w * tm_stride holds the
-// 64 cell masks of word w.  A round takes the first n of 64 entries from its
+// Where the wavefronts of a run kernel take the cell masks of a word from.
+// Packed: Tm + w * tm_stride holds the 64 masks of word w (k_pack_cells, or a
+// batch's pack).
+template <typename M>
+struct PackedCells {
+    const M *Tm;
+    uint64_t tm_stride;
+    uint32_t off;  // this lane's mask in a word, in bytes
+    typedef M Raw;
+    __device__ __forceinline__ PackedCells(const M *t, uint64_t stride, uint32_t lane)
+        : Tm(t), tm_stride(stride), off(lane * (uint32_t)sizeof(M)) {}
+    // unconditional: a round that builds no tables loads one line of its last word
+    __device__ __forceinline__ void load(Raw &r, uint32_t word, uint32_t, bool build) const
+    {
+        const __amdgpu_buffer_rsrc_t rs = uniform_rsrc(Tm + (uint64_t)word * tm_stride);
+        const int at = build ? (int)off : 0;
+        if constexpr (sizeof(M) == 8) r = __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(rs, at, 0, 0));
+        else r = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, at, 0, 0);
+    }
+    __device__ __forceinline__ M mask(const Raw &r) const { return r; }
+    // the register counts as used (see tile_accumulate)
+    static __device__ __forceinline__ void keep(const Raw &r)
+    {
+        if constexpr (sizeof(M) == 8) asm volatile("" ::"v"((uint32_t)r), "v"((uint32_t)(r >> 32)));
+        else asm volatile("" ::"v"(r));
+    }
+};
+
+// From the frame itself: each lane reads its own cell's n_props bytes, in C
+// pieces of B bytes (16: 16 C - 15 .. 16 C propositions; 8 and 4, C = 2: 8 .. 15
+// and 4 .. 7), the last one ending with the cell's last byte, so that it may
+// repeat bytes of the one before and none outside the cell is read.
+template <typename M, uint32_t B, uint32_t C>
+struct FrameCells {
+    const uint8_t *O;
+    uint32_t n_props;
+    uint32_t off;  // this lane's cell from the word's first, in bytes
+    struct Raw {
+        uint32_t d[C][B / 4];
+    };
+    __device__ __forceinline__ FrameCells(const uint8_t *frame, uint32_t np, uint32_t nx, uint32_t morton, uint32_t lane)
+        : O(frame), n_props(np),
+          off((morton ? word_z(lane & 7u, lane >> 3) : (lane >> 3) * nx + (lane & 7u)) * np) {}
+    __device__ __forceinline__ void load(Raw &r, uint32_t, uint32_t cell, bool build) const
+    {
+        global_u8 *src = (global_u8 *)O + (uint64_t)cell * n_props + (build ? off : 0u);
+#pragma unroll
+        for (uint32_t k = 0; k < C; ++k) {
+            global_u8 *p = src + (k + 1 < C ? B * k : n_props - B);
+            if constexpr (B == 16) {
+                const u32x4_any v = load_any<u32x4_any>(p);
+                r.d[k][0] = v.x, r.d[k][1] = v.y, r.d[k][2] = v.z, r.d[k][3] = v.w;
+            } else if constexpr (B == 8) {
+                const u32x2_any v = load_any<u32x2_any>(p);
+                r.d[k][0] = v.x, r.d[k][1] = v.y;
+            } else {
+                r.d[k][0] = load_any<u32_any>(p);
+            }
+        }
+    }
+    __device__ __forceinline__ M mask(const Raw &r) const
+    {
+        M m = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < C; ++k) {
+            const uint32_t *d = r.d[k];
+            const uint32_t b = B == 16 ? nz_bytes16(d[0], d[1], d[B / 8], d[B / 4 - 1]) : B == 8 ? nz_bytes8(d[0], d[B / 4 - 1]) : nz_bytes(d[0]);
+            m |= (M)b << (k + 1 < C ? B * k : n_props - B);
+        }
+        return m;
+    }
+    static __device__ __forceinline__ void keep(const Raw &r)
+    {
+#pragma unroll
+        for (uint32_t k = 0; k < C; ++k)
+#pragma unroll
+            for (uint32_t j = 0; j < B / 4; ++j) asm volatile("" ::"v"(r.d[k][j]));
+    }
+};
+
+// tile_accumulate for a layout in run entries, the cell masks coming from
+// `cells`.  A round takes the first n of 64 entries from its
 // own offset (n in the record's lane_hi; no lane is skipped at the front), in
 // at most two segments, and builds at most one segment's run tables.  Each
 // entry says itself which of the wavefront's two table slots it reads.
@@ -653,11 +735,10 @@ __device__ __forceinline__ void tile_accumulate(const SpTask *__restrict__ wg_ta
 // 80 MB against 99; packing 5.2 us against 7.1, as it writes 512 bytes per
 // word and not 2 KiB of tables.  50k x 256^2 x 32: 7.0 us and 3.0 against 7.7
 // and 4.2.  Three and four rounds in flight: 26.2 and 27.5 us.
-template <int WAVES, typename M>
+template <int WAVES, typename M, typename Cells>
 __device__ __forceinline__ void run_accumulate(const SpTask *__restrict__ wg_tasks,
                                                const SpRound *__restrict__ rounds,
-                                               const uint64_t *__restrict__ ent, const M *__restrict__ Tm,
-                                               uint64_t tm_stride, void *lds)
+                                               const uint64_t *__restrict__ ent, const Cells &cells, void *lds)
 {
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -674,30 +755,25 @@ __device__ __forceinline__ void run_accumulate(const SpTask *__restrict__ wg_tas
         uint32_t rec;   // lanes 0-3: the record of the stage's next round
         uint32_t meta;
         uint64_t x;     // this lane's entry
-        M m;            // its cell of the word whose tables the round builds
+        typename Cells::Raw m;  // its cell of the word whose tables the round builds
     };
     // the loads as in tile_accumulate: unconditional, through raw buffer
     // resources, the entries and masks of a round kRunStages - 1 rounds ahead
     // and its record kRunStages rounds before that
     const __amdgpu_buffer_rsrc_t r_rec = uniform_rsrc(rounds + round0);
     const __amdgpu_buffer_rsrc_t r_ent = uniform_rsrc(ent + tk_lo);
-    const uint32_t o_rec = (lane & 3u) * 4u, o_ent = lane * 8u, o_m = lane * (uint32_t)sizeof(M);
+    const uint32_t o_rec = (lane & 3u) * 4u, o_ent = lane * 8u;
     auto load_rec = [&](uint32_t i) {
         return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r_rec, (int)o_rec, (int)(min(i, n - 1) * 16u), 0);
     };
     auto fetch = [&](Stage &st, uint32_t i) {
         const uint32_t e_off = (uint32_t)__builtin_amdgcn_readlane((int)st.rec, 0);
         const uint32_t tword = (uint32_t)__builtin_amdgcn_readlane((int)st.rec, 1);
+        const uint32_t tcell = (uint32_t)__builtin_amdgcn_readlane((int)st.rec, 2);
         st.meta = (uint32_t)__builtin_amdgcn_readlane((int)st.rec, 3);
         st.rec = load_rec(i + kRunStages);
         st.x = __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(r_ent, (int)o_ent, (int)(e_off * 8u), 0));
-        // a round that builds no tables loads one line of its last word
-        const __amdgpu_buffer_rsrc_t r_m = uniform_rsrc(Tm + (uint64_t)tword * tm_stride);
-        const uint32_t ml = (st.meta & (kMetaBuild0 | kMetaBuild1)) ? o_m : 0u;
-        if constexpr (sizeof(M) == 8)
-            st.m = __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(r_m, (int)ml, 0, 0));
-        else
-            st.m = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r_m, (int)ml, 0, 0);
+        cells.load(st.m, tword, tcell, (st.meta & (kMetaBuild0 | kMetaBuild1)) != 0);
     };
     uint32_t slot_a, slot_b;
     asm("v_mov_b32 %0, %1" : "=v"(slot_a) : "s"(lds_addr(tab)));
@@ -706,7 +782,7 @@ __device__ __forceinline__ void run_accumulate(const SpTask *__restrict__ wg_tas
         const uint32_t meta = st.meta;
         if (meta & (kMetaBuild0 | kMetaBuild1)) {
             const uint32_t s = ((meta & kMetaSlot0) ? 1u : 0u) ^ ((meta & kMetaBuild1) ? 1u : 0u);
-            build_runs<M>(st.m, tab + s * kRunWords, lane);
+            build_runs<M>(cells.mask(st.m), tab + s * kRunWords, lane);
         }
         __builtin_amdgcn_wave_barrier();
         const uint32_t lo = (uint32_t)st.x, hi = (uint32_t)(st.x >> 32);
@@ -728,11 +804,7 @@ __device__ __forceinline__ void run_accumulate(const SpTask *__restrict__ wg_tas
             __hip_atomic_fetch_or(acc + __builtin_amdgcn_ubfe(hi, kRunRowBit - 32, 13u), a, __ATOMIC_RELAXED,
                                   __HIP_MEMORY_SCOPE_WORKGROUP);
         __builtin_amdgcn_wave_barrier();  // later builds overwrite these tables
-        // counts as used also when no tables were built (see tile_accumulate)
-        if constexpr (sizeof(M) == 8)
-            asm volatile("" ::"v"((uint32_t)st.m), "v"((uint32_t)(st.m >> 32)));
-        else
-            asm volatile("" ::"v"(st.m));
+        Cells::keep(st.m);  // also when no tables were built
     };
     Stage st[kRunStages];
     if (n > 0) {
@@ -806,6 +878,19 @@ k_label_tiles(const uint32_t *__restrict__ block_tile, const SpTask *__restrict_
     }
 }
 
+// The tile's labels as its partials, compact or of every row.
+template <int WAVES, typename M>
+__device__ __forceinline__ void tile_partials(const void *lds, uint32_t tile, M *__restrict__ P,
+                                              const uint32_t *__restrict__ tile_slot, const uint16_t *__restrict__ slot_row)
+{
+    if (tile_slot) {
+        const uint32_t s0 = tile_slot[tile], s1 = tile_slot[tile + 1];
+        write_partials_compact<WAVES, M>(lds, P + s0, slot_row + s0, s1 - s0);
+    } else {
+        write_partials<WAVES, M>(lds, P + (uint64_t)tile * kRowBlock);
+    }
+}
+
 // k_label_tiles for a layout in run entries (Tm: k_pack_cells' masks).
 template <int WAVES, typename M>
 __global__ void __launch_bounds__(64 * WAVES, sizeof(M) == 8 ? 1 : 2)
@@ -815,13 +900,38 @@ k_label_runs(const uint32_t *__restrict__ block_tile, const SpTask *__restrict__
 {
     extern __shared__ uint64_t lds[];
     const uint32_t tile = block_tile[blockIdx.x];
-    run_accumulate<WAVES, M>(tasks_launch + (uint64_t)blockIdx.x * WAVES, rounds, ent, Tm, 64, lds);
-    if (tile_slot) {
-        const uint32_t s0 = tile_slot[tile], s1 = tile_slot[tile + 1];
-        write_partials_compact<WAVES, M>(lds, P + s0, slot_row + s0, s1 - s0);
-    } else {
-        write_partials<WAVES, M>(lds, P + (uint64_t)tile * kRowBlock);
-    }
+    const PackedCells<M> cells(Tm, 64, threadIdx.x & 63);
+    run_accumulate<WAVES, M>(tasks_launch + (uint64_t)blockIdx.x * WAVES, rounds, ent, cells, lds);
+    tile_partials<WAVES, M>(lds, tile, P, tile_slot, slot_row);
+}
+
+// The same with the masks formed from O (FrameCells), for frames where
+// tiles_pack says so: no pack kernel runs before.
+template <int WAVES, typename M, uint32_t B, uint32_t C>
+__global__ void __launch_bounds__(64 * WAVES, sizeof(M) == 8 ? 1 : 2)
+k_label_runs_frame(const uint32_t *__restrict__ block_tile, const SpTask *__restrict__ tasks_launch,
+                   const SpRound *__restrict__ rounds, const uint64_t *__restrict__ ent, const uint8_t *__restrict__ O,
+                   uint32_t n_props, uint32_t nx, uint32_t morton, M *__restrict__ P,
+                   const uint32_t *__restrict__ tile_slot, const uint16_t *__restrict__ slot_row)
+{
+    extern __shared__ uint64_t lds[];
+    const uint32_t tile = block_tile[blockIdx.x];
+    const FrameCells<M, B, C> cells(O, n_props, nx, morton, threadIdx.x & 63);
+    run_accumulate<WAVES, M>(tasks_launch + (uint64_t)blockIdx.x * WAVES, rounds, ent, cells, lds);
+    tile_partials<WAVES, M>(lds, tile, P, tile_slot, slot_row);
+}
+
+// k_label_runs_frame for n_props bytes a cell.
+template <typename M>
+auto label_runs_frame(uint32_t n_props)
+{
+    if constexpr (sizeof(M) == 4)
+        return n_props < 8    ? &k_label_runs_frame<kTileWaves, M, 4, 2>
+               : n_props < 16 ? &k_label_runs_frame<kTileWaves, M, 8, 2>
+               : n_props > 16 ? &k_label_runs_frame<kTileWaves, M, 16, 2>
+                              : &k_label_runs_frame<kTileWaves, M, 16, 1>;
+    else
+        return n_props > 48 ? &k_label_runs_frame<kTileWaves, M, 16, 4> : &k_label_runs_frame<kTileWaves, M, 16, 3>;
 }
 
 // Frames of at most NP <= 4 propositions (the direct-mask kernel).  A label
@@ -1034,7 +1144,9 @@ __device__ __forceinline__ void batch_tile(const GroupDesc *__restrict__ groups,
     const GroupDesc &g = groups[it.group];
     if (g.sp_ent)
         run_accumulate<WAVES, uint64_t>(g.sp_tasks + (uint64_t)it.tile * WAVES, g.sp_rounds, g.sp_ent,
-                                        g.Ow + (uint64_t)it.gi * 64, (uint64_t)g.G64 * 64, lds);
+                                        PackedCells<uint64_t>(g.Ow + (uint64_t)it.gi * 64, (uint64_t)g.G64 * 64,
+                                                              threadIdx.x & 63),
+                                        lds);
     else
         tile_accumulate<WAVES, uint64_t>(g.sp_tasks + (uint64_t)it.tile * WAVES, g.sp_rounds, g.sp_row, g.sp_val,
                                          g.Ow + (uint64_t)it.gi * 256, (uint64_t)g.G64 * 256, lds);
@@ -1965,6 +2077,21 @@ lbl_status sparse_part(const uint64_t *T, uint32_t row_stride, uint64_t n_rows, 
     return LBL_OK;
 }
 
+// A segment costs a cache access per lane and piece loaded (more where pieces
+// straddle dwords); the pack kernel it saves costs its launch and 3 to 5 us.  Us
+// per frame with the pack kernel and without, segments x pieces in brackets:
+// 1,000 x 64^2 x 8 13.4, 12.4 (128); 57,000 x 128^2 x 40 14.9, 12.0 (5k);
+// 50,000 x 256^2 x 32 15.0, 14.1 (14k); 57,000 x 256^2 x 64 16.4, 15.8 (29k);
+// 25,000 x 512^2 x 40 17.3, 15.6 (48k); 120,000 x 256^2 x 64 19.1, 21.4 (60k);
+// 57,000 x 512^2 x 64 21.5, 22.5 (112k).  Unaligned: 40,000 x 256^2 x 17 15.0,
+// 16.0 (10k); 120,000 x 256^2 x 17 16.6, 22.4 (30k); 75,003 x 328^2 x 37 17.2,
+// 21.2 (50k).
+bool tiles_pack(uint64_t n_seg, uint32_t n_props, bool aligned)
+{
+    const uint64_t pieces = n_props < 16 ? 2 : (n_props + 15) / 16;
+    return n_seg <= (1ull << 32) && n_seg * pieces * (aligned ? 1 : 8) <= 50000;
+}
+
 // Measured on 50k rows of 30 words of 64 random cells (label kernel, 64
 // propositions): at 1.15 run entries per word 11.1 us, nibble entries 11.1;
 // at 1.45, 12.1 against 11.6; at 2.0, 13.9 against 11.8.  Swept footprints
@@ -2100,6 +2227,12 @@ lbl_status sparse_assemble(lbl_abs *a, std::vector<SparsePart> &parts)
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRunLds));
     LBL_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_label_runs<kTileWaves, uint32_t>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRunLds32));
+    for (uint32_t np : {4u, 8u, 16u, 32u})
+        LBL_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(label_runs_frame<uint32_t>(np)),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRunLds32));
+    for (uint32_t np : {48u, 64u})
+        LBL_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(label_runs_frame<uint64_t>(np)),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRunLds));
     const uint32_t n_cu = (uint32_t)device_cu_count();
     sp->tilings.resize(kNarrowTiling + 1);
     std::vector<uint16_t> rows_host(nnz);
@@ -2120,6 +2253,9 @@ lbl_status sparse_assemble(lbl_abs *a, std::vector<SparsePart> &parts)
                                             : std::vector<uint32_t>(sp->n_rb, 1u << (i - 1));
         TilingHost h;
         (runs ? make_run_tiling : make_tiling)(tile_start, seg_word, rb_seg, k, &h);
+        if (runs)
+            for (SpRound &r : h.rounds)
+                r.tcell = a->order.morton ? r.tword * 64u : a->order.word_cell[(uint64_t)r.tword * 64];
         // the tile kernels address a task's entries (8 bytes each) and round
         // records with 32-bit byte offsets
         for (const SpTask &t : h.tasks)
@@ -2224,17 +2360,26 @@ lbl_status run_swm_t(const lbl_abs *a, const SpTiling &tl, const uint8_t *O, uin
         if (spans) lbl::span_end(b, st, kind);
     };
     const dim3 pack_grid((unsigned)(((uint64_t)sp.n_used * 64 + 255) / 256));
-    void *spn = span_begin(s);
-    if (sp.ent)
-        hipLaunchKernelGGL(k_pack_cells<M>, pack_grid, dim3(256), 0, s, O, n_props, sp.pack_first, a->nx,
-                           (uint32_t)a->order.morton, sp.used_words, sp.n_used, Tg);
-    else
-        hipLaunchKernelGGL(k_pack_tables<M>, pack_grid, dim3(256), 0, s, O, n_props, sp.pack_first, a->nx,
-                           (uint32_t)a->order.morton, sp.used_words, sp.n_used, Tg);
-    LBL_HIP_TRY(hipGetLastError());
-    span_end(spn, s, 0);
+    const bool from_frame = sp.ent && n_props >= 4 && 8ull * a->nx * n_props < (1ull << 31) &&  // 32-bit offsets
+                            tiles_pack(sp.n_segments, n_props, n_props % 4 == 0 && reinterpret_cast<uintptr_t>(O) % 4 == 0);
+    void *spn = nullptr;
+    if (!from_frame) {
+        spn = span_begin(s);
+        if (sp.ent)
+            hipLaunchKernelGGL(k_pack_cells<M>, pack_grid, dim3(256), 0, s, O, n_props, sp.pack_first, a->nx,
+                               (uint32_t)a->order.morton, sp.used_words, sp.n_used, Tg);
+        else
+            hipLaunchKernelGGL(k_pack_tables<M>, pack_grid, dim3(256), 0, s, O, n_props, sp.pack_first, a->nx,
+                               (uint32_t)a->order.morton, sp.used_words, sp.n_used, Tg);
+        LBL_HIP_TRY(hipGetLastError());
+        span_end(spn, s, 0);
+    }
     spn = span_begin(s);
-    if (sp.ent)
+    if (from_frame)
+        hipLaunchKernelGGL(label_runs_frame<M>(n_props), dim3(tl.n_tiles), dim3(64 * kTileWaves),
+                           sizeof(M) == 8 ? kRunLds : kRunLds32, s, tl.block_tile, tl.tasks_launch, tl.rounds, sp.ent, O,
+                           n_props, a->nx, (uint32_t)a->order.morton, P, tl.tile_slot, tl.slot_row);
+    else if (sp.ent)
         hipLaunchKernelGGL((k_label_runs<kTileWaves, M>), dim3(tl.n_tiles), dim3(64 * kTileWaves),
                            sizeof(M) == 8 ? kRunLds : kRunLds32, s, tl.block_tile, tl.tasks_launch, tl.rounds, sp.ent,
                            Tg, P, tl.tile_slot, tl.slot_row);
