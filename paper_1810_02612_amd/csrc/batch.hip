@@ -405,7 +405,14 @@ void plan_finalize(BatchPlan &p, const BatchTile &tile)
                 for (uint32_t k = 0; k < kXcds && pos[y] >= p.xcd_start[y + 1]; ++k) y = (x + k) % kXcds;
                 if (pos[y] < p.xcd_start[y + 1]) p.launch.push_back(pos[y]++);
             }
-        const uint64_t R = 128;  // rows per combine item (a multiple of 64)
+        // rows per combine item: 64, or 256 where that still leaves thousands of
+        // wavefronts.  Us per batch at 64 and 256: 25k rows x 128^2 x 4 (1,173
+        // chunks of 64) 17.2, 20.7; six maps x 1 (8,400) 62.7, 65.9; x 3 155.5,
+        // 154.2; x 16 (82,000) 515, 506
+        uint64_t chunks = 0;
+        for (const GroupDesc &d : p.groups)
+            if (!d.fused) chunks += d.G64 * ((d.n_traj + 63) / 64);
+        const uint64_t R = chunks >= 12288 ? 256 : 64;
         for (uint32_t g = 0; g < p.groups.size(); ++g)
             if (!p.groups[g].fused)
                 for (uint32_t gi = 0; gi < p.groups[g].G64; ++gi)

@@ -1372,34 +1372,98 @@ __device__ __forceinline__ uint64_t row_partials(const M *__restrict__ P, const 
     return bits;
 }
 
-// One wavefront per (pass, lane group, rows [row0, row1)), 64 rows at a
-// time: lane j ORs the partials of row t0 + j (the 64 columns of the lane
-// group), then every job of the lane group gets its block of label bytes for
-// those rows (emit_block).  Each byte of L belongs to one job, one row range
-// and one lane group, so exactly one wavefront writes it.
+// row_slots_or of W rows at once, two loads of each in flight: their chains of
+// loads (offsets, slots, partials) run side by side.  Rows at or past n_rows
+// have no slots.
+template <typename M, uint32_t W>
+__device__ __forceinline__ void rows_slots_or(const M *__restrict__ P, const uint32_t *__restrict__ off,
+                                              const uint32_t *__restrict__ slots, const uint64_t (&t)[W], uint64_t n_rows,
+                                              uint64_t (&bits)[W])
+{
+    typedef __attribute__((address_space(1))) const M gm;
+    typedef __attribute__((address_space(1))) const uint32_t gu32;
+    const gm *Pg = (const gm *)P;
+    const gu32 *og = (const gu32 *)off, *sg = (const gu32 *)slots;
+    uint32_t k[W], e[W];
+#pragma unroll
+    for (uint32_t w = 0; w < W; ++w) {
+        const uint64_t r = min(t[w], n_rows - 1);
+        k[w] = og[r];
+        e[w] = og[r + 1];
+    }
+    bool more = false;
+#pragma unroll
+    for (uint32_t w = 0; w < W; ++w) {
+        bits[w] = 0;
+        if (t[w] >= n_rows) e[w] = k[w];
+        more = more || k[w] < e[w];
+    }
+    while (more) {
+        M v[W][2];
+        // some row has slots, so slot 0 is there to be read (and dropped) by
+        // rows without more
+#pragma unroll
+        for (uint32_t w = 0; w < W; ++w)
+#pragma unroll
+            for (uint32_t j = 0; j < 2; ++j) v[w][j] = Pg[sg[k[w] + j < e[w] ? k[w] + j : 0u]];
+        more = false;
+#pragma unroll
+        for (uint32_t w = 0; w < W; ++w) {
+#pragma unroll
+            for (uint32_t j = 0; j < 2; ++j) bits[w] |= k[w] + j < e[w] ? (uint64_t)v[w][j] : 0ull;
+            k[w] += 2;
+            more = more || k[w] < e[w];
+        }
+    }
+}
+
+// Label bytes of rows [row0, row1) (at most 64 C) of a lane group: lane j ORs
+// the partials of rows row0 + j, row0 + 64 + j, ... (the group's 64 columns), then
+// every job of the group gets its blocks of label bytes (emit_block).
+template <uint32_t C>
+__device__ __forceinline__ void combine_rows(const GroupDesc &g, uint32_t gi, uint64_t row0, uint64_t row1, uint32_t lane,
+                                             uint32_t *stage)
+{
+    const bool compact = g.tile_slot != nullptr;
+    const uint64_t *Pg = g.P + (uint64_t)gi * (compact ? g.n_slots : (uint64_t)g.n_tiles * kRowBlock);
+    const uint32_t s0 = __builtin_amdgcn_readfirstlane((int)g.lg_seg[gi]);
+    const uint32_t s1 = __builtin_amdgcn_readfirstlane((int)g.lg_seg[gi + 1]);
+    uint64_t bits[C], t[C];
+#pragma unroll
+    for (uint32_t c = 0; c < C; ++c) t[c] = row0 + 64 * c + lane;
+    if (compact) {
+        rows_slots_or(Pg, g.row_slot_off, g.row_slots, t, row1, bits);
+    } else {
+#pragma unroll
+        for (uint32_t c = 0; c < C; ++c) bits[c] = t[c] < row1 ? row_partials(Pg, g.sp_rb_tile, t[c]) : 0ull;
+    }
+    for (uint32_t sgi = s0; sgi < s1; ++sgi) {
+        const SegDesc d = uniform_seg(g.segs, sgi);
+#pragma unroll
+        for (uint32_t c = 0; c < C; ++c) {
+            const uint64_t t0 = row0 + 64 * c;
+            if (t0 >= row1) break;  // uniform
+            const uint64_t v = d.n_props >= 64 ? bits[c] : (bits[c] >> d.bit) & ((1ull << d.n_props) - 1ull);
+            emit_block(stage, lane, (uint32_t)min<uint64_t>(64, row1 - t0), v, d.L + t0 * d.n_props, d.n_props);
+        }
+    }
+}
+
+// One wavefront per (pass, lane group, rows [row0, row1)), up to 256 rows.  Each
+// byte of L belongs to one job, one row range and one lane group, so exactly
+// one wavefront writes it.
+//
+// Bound by the chain of its loads (item, descriptors, offsets, slots,
+// partials): with 128 rows to an item, 64 after 64, six maps x 16 frames took
+// 103 us, now 76.
 __global__ void __launch_bounds__(64)
 k_combine_batch(const GroupDesc *__restrict__ groups, const CombineItem *__restrict__ items)
 {
     __shared__ uint32_t stage[kStageWords];
-    const uint32_t lane = threadIdx.x;
     const CombineItem it = items[blockIdx.x];
     const GroupDesc &g = groups[it.group];
-    const bool compact = g.tile_slot != nullptr;
-    const uint64_t *Pg = g.P + (uint64_t)it.gi * (compact ? g.n_slots : (uint64_t)g.n_tiles * kRowBlock);
-    const uint32_t s0 = __builtin_amdgcn_readfirstlane((int)g.lg_seg[it.gi]);
-    const uint32_t s1 = __builtin_amdgcn_readfirstlane((int)g.lg_seg[it.gi + 1]);
-    for (uint64_t t0 = it.row0; t0 < it.row1; t0 += 64) {
-        const uint64_t t = t0 + lane;
-        uint64_t bits = 0;
-        if (t < it.row1)
-            bits = compact ? row_slots_or(Pg, g.row_slot_off, g.row_slots, t) : row_partials(Pg, g.sp_rb_tile, t);
-        const uint32_t n = (uint32_t)min<uint64_t>(64, it.row1 - t0);
-        for (uint32_t sgi = s0; sgi < s1; ++sgi) {
-            const SegDesc d = uniform_seg(g.segs, sgi);
-            const uint64_t v = d.n_props >= 64 ? bits : (bits >> d.bit) & ((1ull << d.n_props) - 1ull);
-            emit_block(stage, lane, n, v, d.L + t0 * d.n_props, d.n_props);
-        }
-    }
+    if (it.row1 - it.row0 <= 64) combine_rows<1>(g, it.gi, it.row0, it.row1, threadIdx.x, stage);
+    else combine_rows<4>(g, it.gi, it.row0, it.row1, threadIdx.x, stage);
 }
 
 // Rows' label bytes from their partials.  One wavefront takes 64 consecutive
