@@ -39,7 +39,8 @@
 // steps with k_pack_cells, which writes the cells' masks, and k_label_runs,
 // whose wavefronts build the tables of 8-cell rows themselves; where there are
 // few segments (tiles_pack) k_label_runs_frame forms the masks from O as well,
-// and there is no pack kernel.
+// and there is no pack kernel; the smallest frames (one_launch_pays) take
+// k_label_runs_whole alone.
 // Frames of at most 4 propositions take two other kernels instead:
 //   k_pack_masks   O -> NP proposition masks per used word (bit b = cell b);
 //                  the grid also zeroes L.
@@ -52,6 +53,7 @@
 #include <algorithm>
 #include <cmath>
 #include <queue>
+#include <type_traits>
 
 #include "batch.h"
 #include "emit.h"
@@ -921,17 +923,63 @@ k_label_runs_frame(const uint32_t *__restrict__ block_tile, const SpTask *__rest
     tile_partials<WAVES, M>(lds, tile, P, tile_slot, slot_row);
 }
 
-// k_label_runs_frame for n_props bytes a cell.
+// The whole of a small frame (one_launch_pays) in one launch: the workgroup
+// takes every entry of row block blockIdx.x (the tiling of one tile per row
+// block), forms the masks from O, and writes its rows' label bytes from the
+// accumulators.
+template <int WAVES, typename M, uint32_t B, uint32_t C>
+__global__ void __launch_bounds__(64 * WAVES, sizeof(M) == 8 ? 1 : 2)
+k_label_runs_whole(const SpTask *__restrict__ tasks, const SpRound *__restrict__ rounds, const uint64_t *__restrict__ ent,
+                   const uint8_t *__restrict__ O, uint32_t n_props, uint32_t nx, uint32_t morton, uint64_t n_traj,
+                   uint8_t *__restrict__ L)
+{
+    extern __shared__ uint64_t lds[];
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const FrameCells<M, B, C> cells(O, n_props, nx, morton, lane);
+    run_accumulate<WAVES, M>(tasks + (uint64_t)blockIdx.x * WAVES, rounds, ent, cells, lds);
+    // wavefront w writes the 64-row chunks w, w + WAVES, ..., staged in the LDS
+    // its tables used
+    const M *acc = reinterpret_cast<const M *>(lds);
+    static_assert(kStageWords * 4 <= 2 * kRunWords * sizeof(M), "a stage must fit in the wavefront's tables");
+    uint32_t *stage = reinterpret_cast<uint32_t *>(reinterpret_cast<M *>(lds) + kRowBlock + wave * (2 * kRunWords));
+    const uint64_t t0 = (uint64_t)blockIdx.x * kRowBlock;
+    const uint32_t n_rows = (uint32_t)min<uint64_t>(kRowBlock, n_traj - t0);
+    const bool v16 = (n_props & 15u) == 0 && (reinterpret_cast<uintptr_t>(L) & 15u) == 0;
+    for (uint32_t c0 = wave * 64; c0 < n_rows; c0 += 64 * WAVES) {
+        const uint32_t n = min(64u, n_rows - c0);
+        const uint64_t bits = lane < n ? acc[c0 + lane] : 0;
+        if (v16) emit_units(lane, n, bits, L + (t0 + c0) * n_props, n_props / 16);
+        else emit_block(stage, lane, n, bits, L + (t0 + c0) * n_props, n_props);
+    }
+}
+
+// k_label_runs_frame, or k_label_runs_whole, for n_props bytes a cell: calls
+// f with the kernels' B and C.
+template <typename M, typename F>
+auto for_pieces(uint32_t n_props, F f)
+{
+    typedef std::integral_constant<uint32_t, 16> P16;
+    typedef std::integral_constant<uint32_t, 2> Two;
+    if constexpr (sizeof(M) == 4) {
+        if (n_props < 8) return f(std::integral_constant<uint32_t, 4>(), Two());
+        if (n_props < 16) return f(std::integral_constant<uint32_t, 8>(), Two());
+        if (n_props > 16) return f(P16(), Two());
+        return f(P16(), std::integral_constant<uint32_t, 1>());
+    } else {
+        if (n_props > 48) return f(P16(), std::integral_constant<uint32_t, 4>());
+        return f(P16(), std::integral_constant<uint32_t, 3>());
+    }
+}
 template <typename M>
 auto label_runs_frame(uint32_t n_props)
 {
-    if constexpr (sizeof(M) == 4)
-        return n_props < 8    ? &k_label_runs_frame<kTileWaves, M, 4, 2>
-               : n_props < 16 ? &k_label_runs_frame<kTileWaves, M, 8, 2>
-               : n_props > 16 ? &k_label_runs_frame<kTileWaves, M, 16, 2>
-                              : &k_label_runs_frame<kTileWaves, M, 16, 1>;
-    else
-        return n_props > 48 ? &k_label_runs_frame<kTileWaves, M, 16, 4> : &k_label_runs_frame<kTileWaves, M, 16, 3>;
+    return for_pieces<M>(n_props, [](auto b, auto c) { return &k_label_runs_frame<kTileWaves, M, b.value, c.value>; });
+}
+template <typename M>
+auto label_runs_whole(uint32_t n_props)
+{
+    return for_pieces<M>(n_props, [](auto b, auto c) { return &k_label_runs_whole<kTileWaves, M, b.value, c.value>; });
 }
 
 // Frames of at most NP <= 4 propositions (the direct-mask kernel).  A label
@@ -2141,6 +2189,17 @@ lbl_status sparse_part(const uint64_t *T, uint32_t row_stride, uint64_t n_rows, 
     return LBL_OK;
 }
 
+// One workgroup walks all rounds, some 64 entries each, and builds every
+// segment's tables; two launches cost 3 to 4 us more than one.  Us per frame
+// with two launches and one, rounds + segments x pieces / 2 in brackets: 1,000 x
+// 64^2 x 8 12.2, 8.6 (182); x 64 12.6, 11.3 (246); 2,000 x 64^2 x 8 11.9, 9.0
+// (299); 4,000 x 64^2 x 12 12.1, 15.7 (530); 2,000 x 128^2 x 40 12.3, 21.8 (800).
+bool one_launch_pays(uint64_t n_ent, uint64_t n_seg, uint32_t n_rb, uint32_t n_props)
+{
+    const uint64_t pieces = n_props < 16 ? 2 : (n_props + 15) / 16;
+    return n_rb == 1 && n_ent / 64 + n_seg * pieces / 2 <= 320;
+}
+
 // A segment costs a cache access per lane and piece loaded (more where pieces
 // straddle dwords); the pack kernel it saves costs its launch and 3 to 5 us.  Us
 // per frame with the pack kernel and without, segments x pieces in brackets:
@@ -2292,11 +2351,13 @@ lbl_status sparse_assemble(lbl_abs *a, std::vector<SparsePart> &parts)
     LBL_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_label_runs<kTileWaves, uint32_t>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRunLds32));
     for (uint32_t np : {4u, 8u, 16u, 32u})
-        LBL_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(label_runs_frame<uint32_t>(np)),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRunLds32));
+        for (const void *f : {reinterpret_cast<const void *>(label_runs_frame<uint32_t>(np)),
+                              reinterpret_cast<const void *>(label_runs_whole<uint32_t>(np))})
+            LBL_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRunLds32));
     for (uint32_t np : {48u, 64u})
-        LBL_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(label_runs_frame<uint64_t>(np)),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRunLds));
+        for (const void *f : {reinterpret_cast<const void *>(label_runs_frame<uint64_t>(np)),
+                              reinterpret_cast<const void *>(label_runs_whole<uint64_t>(np))})
+            LBL_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRunLds));
     const uint32_t n_cu = (uint32_t)device_cu_count();
     sp->tilings.resize(kNarrowTiling + 1);
     std::vector<uint16_t> rows_host(nnz);
@@ -2427,6 +2488,16 @@ lbl_status run_swm_t(const lbl_abs *a, const SpTiling &tl, const uint8_t *O, uin
     const bool from_frame = sp.ent && n_props >= 4 && 8ull * a->nx * n_props < (1ull << 31) &&  // 32-bit offsets
                             tiles_pack(sp.n_segments, n_props, n_props % 4 == 0 && reinterpret_cast<uintptr_t>(O) % 4 == 0);
     void *spn = nullptr;
+    if (from_frame && one_launch_pays(sp.n_ent, sp.n_segments, sp.n_rb, n_props)) {
+        const SpTiling &one = sp.tilings[1];  // one tile per row block
+        spn = span_begin(s);
+        hipLaunchKernelGGL(label_runs_whole<M>(n_props), dim3(sp.n_rb), dim3(64 * kTileWaves),
+                           sizeof(M) == 8 ? kRunLds : kRunLds32, s, one.tasks, one.rounds, sp.ent, O, n_props, a->nx,
+                           (uint32_t)a->order.morton, a->n_traj, L);
+        LBL_HIP_TRY(hipGetLastError());
+        span_end(spn, s, 1);
+        return LBL_OK;
+    }
     if (!from_frame) {
         spn = span_begin(s);
         if (sp.ent)

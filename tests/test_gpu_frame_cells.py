@@ -24,7 +24,7 @@ def blocks(rng, n_traj, nx, ny):
     return np.concatenate([[0], np.cumsum(on.sum(1))]).astype(np.uint64), (y * nx + x)[on].astype(np.uint32)
 
 
-@pytest.mark.parametrize("n_traj,nx,ny,order", [(50, 8, 8, 0), (9000, 64, 64, 1), (20000, 72, 40, 0), (70000, 256, 256, 0)])
+@pytest.mark.parametrize("n_traj,nx,ny,order", [(50, 8, 8, 0), (700, 72, 40, 0), (2000, 64, 64, 1), (9000, 64, 64, 1), (20000, 72, 40, 0), (70000, 256, 256, 0)])
 def test_masks_from_the_frame(n_traj, nx, ny, order):
     rng = np.random.default_rng([n_traj, nx])
     row_ptr, col = blocks(rng, n_traj, nx, ny)
@@ -49,7 +49,10 @@ def test_masks_from_the_frame(n_traj, nx, ny, order):
             lbl.profile_enable(True)
             lbl.label_frame(h, Od, P, L, flags=lbl.KERNEL_SPARSE)
             torch.cuda.synchronize()
-            packs = lbl.profile_read()["pack_launches"]
+            prof = lbl.profile_read()
+            packs = prof["pack_launches"]
+            if n_traj <= 2000 and P < 16:  # one launch: no combine either
+                assert prof["emit_launches"] == (0 if packs == 0 else 1)
             lbl.profile_enable(False)
             pieces = 2 if P < 16 else -(-P // 16)
             aligned = P % 4 == 0 and (buf.data_ptr() + off) % 4 == 0
