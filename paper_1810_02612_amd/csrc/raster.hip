@@ -2,7 +2,8 @@
 // encoding: a cell's entry is 1 iff the region intersects the cell, read as
 // an overlap of positive area with the closed cell square).
 //
-// One workgroup takes a tile of 512 cells: it lists the shapes whose bounding
+// One workgroup takes a tile of 512 cells (fewer on small grids, wavefronts then
+// sharing the shapes of the same cells): it lists the shapes whose bounding
 // box meets the tile, then one lane per cell tests the listed shapes, collects
 // its propositions as a bit mask, and the wavefront writes its 64 cells' bytes
 // as one block.  Every byte of O is written once.  The tests are exact:
@@ -30,7 +31,7 @@
 namespace lbl {
 namespace {
 
-constexpr uint32_t kRasterWaves = 8;  // wavefronts per tile: 64 cells each
+constexpr uint32_t kRasterWaves = 8;  // wavefronts per workgroup
 
 // The cell coordinate in a z-order index: every second bit of z from bit 0
 // (y) or, of z >> 1, x.
@@ -49,44 +50,49 @@ struct Listed {
     double a, b, c, d;  // rectangle: x from a to b, y from c to d; disc: centre (a, b), c = radius squared
 };
 
-// Tiles of 512 cells: with row-major ids 64 x 8 cells, wavefront w taking row
-// w of the tile; with z-order ids 512 consecutive ids (16 x 32 cells),
-// wavefront w taking ids 64 w ...
+// Tiles of 64 CW cells, CW wavefronts to their cells and 8 / CW to share the
+// listed shapes of the same cells: with row-major ids 64 x CW cells, wavefront w
+// taking row w % CW of the tile; with z-order ids 64 CW consecutive ids,
+// wavefront w taking ids 64 (w % CW) ...
+template <uint32_t CW>
 __global__ void __launch_bounds__(64 * kRasterWaves)
 k_raster_tiles(const lbl_shape *__restrict__ shapes, uint32_t n_shapes, uint32_t nx, uint32_t ny, double cell,
                uint32_t n_props, uint32_t morton, uint32_t n_tiles, uint8_t *__restrict__ O)
 {
 #pragma clang fp contract(off)
     constexpr uint32_t kMost = 64 * kRasterWaves;  // shapes looked at (and listed) at a time
+    constexpr uint32_t kShare = kRasterWaves / CW;
+    __shared__ uint64_t part_mask[kShare > 1 ? kShare - 1 : 1][CW][64];
     __shared__ Listed list[kMost];
     __shared__ uint32_t info[kMost];  // proposition, bit 31: rectangle
     __shared__ uint32_t n_listed;
     __shared__ uint32_t stage[kRasterWaves][kStageWords];
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t cw = wave % CW, part = wave / CW;
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         // the tile's cells [tx, tx + tw) x [ty, ty + th), this lane's cell, the
         // id of the wavefront's first cell and its number of cells
         uint32_t tx, ty, tw, th, ix, iy, n;
         uint64_t id0;
         if (morton) {
-            const uint32_t z0 = tile * kMost, z = z0 + threadIdx.x;
+            const uint32_t z0 = tile * (64 * CW), z = z0 + 64 * cw + lane;
             tx = z_coord(z0 >> 1);
             ty = z_coord(z0);
-            tw = 16;
-            th = 32;
+            tw = CW >= 4 ? 16 : 8;
+            th = CW == 8 ? 32 : CW == 1 ? 8 : 16;
             ix = z_coord(z >> 1);
             iy = z_coord(z);
-            id0 = z0 + 64u * wave;
+            id0 = z0 + 64u * cw;
             n = id0 < (uint64_t)nx * ny ? 64u : 0u;
         } else {
             const uint32_t across = (nx + 63) / 64;
             tx = tile % across * 64u;
-            ty = tile / across * kRasterWaves;
+            ty = tile / across * CW;
             tw = 64;
-            th = kRasterWaves;
+            th = CW;
             ix = tx + lane;
-            iy = ty + wave;
+            iy = ty + cw;
             id0 = (uint64_t)iy * nx + tx;
             n = min(64u, nx - tx);  // ny is a multiple of 8
         }
@@ -117,7 +123,7 @@ k_raster_tiles(const lbl_shape *__restrict__ shapes, uint32_t n_shapes, uint32_t
             }
             __syncthreads();
             const uint32_t m = n_listed;
-            for (uint32_t i = 0; i < m; ++i) {
+            for (uint32_t i = part; i < m; i += kShare) {
                 const uint32_t f = (uint32_t)__builtin_amdgcn_readfirstlane((int)info[i]);
                 const Listed q = list[i];
                 bool hit;
@@ -130,6 +136,14 @@ k_raster_tiles(const lbl_shape *__restrict__ shapes, uint32_t n_shapes, uint32_t
                 mask |= hit ? 1ull << (f & 63u) : 0ull;
             }
             __syncthreads();  // the list is filled again
+        }
+        if constexpr (kShare > 1) {
+            if (part) part_mask[part - 1][cw][lane] = mask;
+            __syncthreads();
+            if (part == 0)
+                for (uint32_t k = 0; k + 1 < kShare; ++k) mask |= part_mask[k][cw][lane];
+            __syncthreads();  // the next tile's masks go to the same place
+            if (part) continue;
         }
         uint8_t *dst = O + id0 * n_props;
         if (n == 0) continue;  // whole wavefronts (every barrier is behind them)
@@ -177,9 +191,19 @@ lbl_status lbl_raster_frame(const lbl_grid *g, double cell_m, const lbl_shape *s
     }
     const bool morton = g->cell_order == LBL_MORTON;
     const uint64_t n_cells = (uint64_t)g->nx * g->ny;
-    const uint64_t tiles = morton ? (n_cells + 64 * kRasterWaves - 1) / (64 * kRasterWaves)
-                                  : (uint64_t)((g->nx + 63) / 64) * (g->ny / kRasterWaves);
-    hipLaunchKernelGGL(k_raster_tiles, dim3((unsigned)std::min<uint64_t>(tiles, 1u << 20)), dim3(64 * kRasterWaves), 0,
+    // the largest tiles that give two workgroups per CU: a tile's shapes are
+    // listed once, but testing them is one wavefront's chain.  Us per call with
+    // tiles of 512, 256, 128 and 64 cells: 64^2 x 39 15.0, 12.1, 12.2, 12.2;
+    // 128^2 x 56 13.5, 11.7, 11.5, 11.9; 392 x 336 x 52 11.7, 11.5, 11.5, 13.0;
+    // 512^2 x 64 13.0, 12.7, 14.7, 19.3
+    auto tiles_of = [&](uint32_t cw) {
+        return morton ? (n_cells + 64 * cw - 1) / (64 * cw) : (uint64_t)((g->nx + 63) / 64) * (g->ny / cw);
+    };
+    uint32_t cw = kRasterWaves;
+    while (cw > 1 && tiles_of(cw) < 512) cw /= 2;
+    const auto kernel = cw == 8 ? &k_raster_tiles<8> : cw == 4 ? &k_raster_tiles<4> : cw == 2 ? &k_raster_tiles<2> : &k_raster_tiles<1>;
+    const uint64_t tiles = tiles_of(cw);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)std::min<uint64_t>(tiles, 1u << 20)), dim3(64 * kRasterWaves), 0,
                        st, d_shapes, (uint32_t)n_shapes, g->nx, g->ny, cell_m, n_props, (uint32_t)morton,
                        (uint32_t)tiles, O);
     LBL_HIP_TRY(hipGetLastError());

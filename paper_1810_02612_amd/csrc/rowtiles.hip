@@ -291,14 +291,15 @@ RowTiles::~RowTiles()
     (void)hipFree(val);
 }
 
-// Measured, us per frame at 64, 128, 256 and 512 rows: 154,776 transitions, 2
-// propositions 17.6 (128), 16.3, 17.0; 1,097,702, 1 proposition 80.8, 68.9,
-// 61.4, and 65 with 1,024.  A tile costs about 5 us of latency (its record,
+// Measured, us per frame at 64, 128 and 256 rows, 2 propositions: 34,639
+// transitions 9.2, 14.0, 13.6; 60,000 10.0, 10.5, 12.8; 125,000 16.2, 13.8,
+// 13.6; 200,000 21.5, 18.5, 18.5; 154,776 with 256 and 512 16.3, 17.0;
+// 1,097,702, 1 proposition, with 128, 256, 512 and 1,024 80.8, 68.9, 61.4, 65.  A tile costs about 5 us of latency (its record,
 // its words, O, and only then its entries), so many small ones are slow, and
 // fewer than about two per CU leave CUs idle.
 uint32_t rows_per_tile(uint64_t n_traj)
 {
-    return n_traj >= (1u << 18) ? 512 : n_traj >= (1u << 16) ? 256 : n_traj >= (1u << 15) ? 128 : 64;
+    return n_traj >= (1u << 18) ? 512 : n_traj >= (1u << 17) ? 256 : n_traj >= (1u << 16) ? 128 : 64;
 }
 
 // Measured against the split of sparse.hip, us per frame: segments of 19 entries

@@ -26,7 +26,7 @@ def rows(rng, n_traj, n):
     return ptr, cells[on].astype(np.uint32)
 
 
-@pytest.mark.parametrize("n_traj", [63, 64, 65, 8191, 8193, 65535, 65537, 262143, 262273])
+@pytest.mark.parametrize("n_traj", [63, 64, 65, 8191, 8193, 65535, 65537, 131073, 262143, 262273])
 @pytest.mark.parametrize("order", [lbl.ROW_MAJOR, lbl.MORTON])
 def test_row_tiles_match_the_oracle(n_traj, order):
     n = 64
@@ -38,7 +38,7 @@ def test_row_tiles_match_the_oracle(n_traj, order):
         ids = np.array([a * 64 + b for a, b in w], np.uint32)
     h = lbl.load_abstraction(n, n, row_ptr, ids[col], lbl.LOAD_SPARSE_ONLY, cell_order=order)
     try:
-        per = 512 if n_traj >= 1 << 18 else 256 if n_traj >= 1 << 16 else 128 if n_traj >= 1 << 15 else 64
+        per = 512 if n_traj >= 1 << 18 else 256 if n_traj >= 1 << 17 else 128 if n_traj >= 1 << 16 else 64
         assert lbl.abstraction_info(h)["sparse_tiles_direct"] == -(-n_traj // per)
         for P in (1, 2, 3, 4):
             O = ((rng.random((n * n, P)) < 0.02) * rng.integers(1, 256, (n * n, P))).astype(np.uint8)
