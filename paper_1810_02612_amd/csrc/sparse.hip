@@ -2207,12 +2207,12 @@ bool one_launch_pays(uint64_t n_ent, uint64_t n_seg, uint32_t n_rb, uint32_t n_p
 // 50,000 x 256^2 x 32 15.0, 14.1 (14k); 57,000 x 256^2 x 64 16.4, 15.8 (29k);
 // 25,000 x 512^2 x 40 17.3, 15.6 (48k); 120,000 x 256^2 x 64 19.1, 21.4 (60k);
 // 57,000 x 512^2 x 64 21.5, 22.5 (112k).  Unaligned: 40,000 x 256^2 x 17 15.0,
-// 16.0 (10k); 44,630 x 128^2 x 26 14.3, 15.1 (3k); 120,000 x 256^2 x 17 16.6, 22.4 (30k); 75,003 x 328^2 x 37 17.2,
+// 16.0 (10k); 12,452 x 96 x 312 x 34 14.0, 11.9 (3k); 120,000 x 256^2 x 17 16.6, 22.4 (30k); 75,003 x 328^2 x 37 17.2,
 // 21.2 (50k).
 bool tiles_pack(uint64_t n_seg, uint32_t n_props, bool aligned)
 {
     const uint64_t pieces = n_props < 16 ? 2 : (n_props + 15) / 16;
-    return n_seg <= (1ull << 32) && n_seg * pieces * (aligned ? 1 : 20) <= 50000;
+    return n_seg <= (1ull << 32) && n_seg * pieces * (aligned ? 1 : 16) <= 50000;
 }
 
 // Measured on 50k rows of 30 words of 64 random cells (label kernel, 64

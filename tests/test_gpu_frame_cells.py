@@ -56,7 +56,7 @@ def test_masks_from_the_frame(n_traj, nx, ny, order):
             lbl.profile_enable(False)
             pieces = 2 if P < 16 else -(-P // 16)
             aligned = P % 4 == 0 and (buf.data_ptr() + off) % 4 == 0
-            assert packs == (0 if n_seg * pieces * (1 if aligned else 20) <= 50000 else 1), (n_seg, P, off)
+            assert packs == (0 if n_seg * pieces * (1 if aligned else 16) <= 50000 else 1), (n_seg, P, off)
             assert np.array_equal(L.cpu().numpy(), oracle.label_csr(row_ptr, col, n, O, threads=8))
     finally:
         lbl.free_abstraction(h)
