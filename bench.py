@@ -328,7 +328,7 @@ def bench_batch(args, lbl, torch, gen, abss, stream):
     single_sparse_s = per_frame(lbl.KERNEL_SPARSE)
     ref = [Ld.clone() for (_, _, _, Ld) in jobs]
     single_s = per_frame(lbl.KERNEL_BITS)
-    # batched: tune the launch for this shape class, then replay the cached graph
+    # batched: tune the launch for this shape class, then launch the batch that is kept
     lbl.tune_batch(jobs, stream=stream)
     for (_, _, _, Ld) in jobs:
         Ld.fill_(5)
