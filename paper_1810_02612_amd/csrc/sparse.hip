@@ -2485,7 +2485,8 @@ lbl_status run_swm_t(const lbl_abs *a, const SpTiling &tl, const uint8_t *O, uin
         if (spans) lbl::span_end(b, st, kind);
     };
     const dim3 pack_grid((unsigned)(((uint64_t)sp.n_used * 64 + 255) / 256));
-    const bool from_frame = sp.ent && n_props >= 4 && 8ull * a->nx * n_props < (1ull << 31) &&  // 32-bit offsets
+    const bool from_frame = sp.ent && n_props >= 4 && (sizeof(M) == 4 || n_props > 32) &&  // what for_pieces covers
+                            8ull * a->nx * n_props < (1ull << 31) &&                       // 32-bit offsets
                             tiles_pack(sp.n_segments, n_props, n_props % 4 == 0 && reinterpret_cast<uintptr_t>(O) % 4 == 0);
     void *spn = nullptr;
     if (from_frame && one_launch_pays(sp.n_ent, sp.n_segments, sp.n_rb, n_props)) {
