@@ -28,6 +28,13 @@ struct SegDesc {
     uint32_t bit;      // first column of the job inside its lane group
 };
 
+// Bytes from a word's first cell to its cell row `run` in a frame with
+// row-major ids, stride8 = nx / 8 * n_props an eighth of a grid row's bytes.  64
+// bits: nx reaches 2^28 (8-row grids of 2^31 cells), so seven rows of 64
+// propositions pass 2^32 from 9,586,984 columns; stride8 stays below 2^32, which
+// makes this one 32 x 32-bit multiply.
+__host__ __device__ inline uint64_t pack_run_offset(uint32_t run, uint32_t stride8) { return ((uint64_t)run * stride8) << 3; }
+
 // Per abstraction group: all jobs on one abstraction, propositions
 // concatenated into G64 groups of 64 lanes.
 struct GroupDesc {

@@ -1283,7 +1283,7 @@ struct PackLane {
 // load leaves the pages the frame lies on.
 template <uint32_t K>
 __device__ __forceinline__ void pack_words(const SegDesc &d, const uint64_t (&cell)[kPackWords], uint32_t run_units,
-                                           uint32_t run_stride, const PackLane &l, uint32_t *stage, uint64_t (&m)[kPackWords])
+                                           uint32_t stride8, const PackLane &l, uint32_t *stage, uint64_t (&m)[kPackWords])
 {
     const uint32_t np = d.n_props, run_bytes = l.run_cells * np;
     // floor(q / run_units) as umulhi(q, magic): exact for q * run_units < 2^32
@@ -1301,14 +1301,13 @@ __device__ __forceinline__ void pack_words(const SegDesc &d, const uint64_t (&ce
     for (uint32_t k = 0; k < K; ++k) {
         const uint32_t u = min(l.lane + 64 * k, last);
         const uint32_t r = __umulhi(u, magic), j = u - r * run_units;
-        // byte offsets fit 32 bits: 7 runs of nx * np bytes (nx * ny < 2^31
-        // cells, np <= 64) plus one run
-        const uint32_t run0 = r * run_stride;
+        const uint64_t run0 = pack_run_offset(r, stride8);
 #pragma unroll
         for (uint32_t w = 0; w < kPackWords; ++w) {
-            const uint32_t at = mis[w] + run0;  // the run's first byte, from base
+            const uint64_t at = mis[w] + run0;  // the run's first byte, from base
+            const uint32_t off = (uint32_t)at & 15u;
             q[w][k] = *reinterpret_cast<__attribute__((address_space(1))) const v4u32 *>(
-                base[w] + min((at & ~15u) + 16 * j, (at + run_bytes - 1) & ~15u));
+                base[w] + (at - off) + min(16 * j, (off + run_bytes - 1) & ~15u));
         }
     }
 #pragma unroll
@@ -1324,7 +1323,7 @@ __device__ __forceinline__ void pack_words(const SegDesc &d, const uint64_t (&ce
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (uint32_t w = 0; w < kPackWords; ++w) {
-        const uint32_t o = 16 * l.run * run_units + ((mis[w] + l.run * run_stride) & 15u) + l.pos * np;
+        const uint32_t o = 16 * l.run * run_units + ((mis[w] + (uint32_t)pack_run_offset(l.run, stride8)) & 15u) + l.pos * np;
         const uint32_t *f = stage + w * kPackStage + (o >> 5);
         const uint32_t lo = __builtin_amdgcn_alignbit(f[1], f[0], o & 31u), hi = __builtin_amdgcn_alignbit(f[2], f[1], o & 31u);
         const uint64_t v = (uint64_t)hi << 32 | lo;
@@ -1375,13 +1374,13 @@ k_pack_batch_tables(const GroupDesc *__restrict__ groups, const PackItem *__rest
         }
         for (uint32_t sgi = s0; sgi < s1; ++sgi) {
             const SegDesc d = uniform_seg(g.segs, sgi);
-            const uint32_t units = (15 + l.run_cells * d.n_props + 15) >> 4, stride = zo ? 0u : g.nx * d.n_props;
+            const uint32_t units = (15 + l.run_cells * d.n_props + 15) >> 4, stride8 = zo ? 0u : g.nx / 8 * d.n_props;
             switch ((l.n_run * units + 63) / 64) {  // uniform
-            case 1: pack_words<1>(d, cell, units, stride, l, stage, m); break;
-            case 2: pack_words<2>(d, cell, units, stride, l, stage, m); break;
-            case 3: pack_words<3>(d, cell, units, stride, l, stage, m); break;
-            case 4: pack_words<4>(d, cell, units, stride, l, stage, m); break;
-            default: pack_words<5>(d, cell, units, stride, l, stage, m); break;
+            case 1: pack_words<1>(d, cell, units, stride8, l, stage, m); break;
+            case 2: pack_words<2>(d, cell, units, stride8, l, stage, m); break;
+            case 3: pack_words<3>(d, cell, units, stride8, l, stage, m); break;
+            case 4: pack_words<4>(d, cell, units, stride8, l, stage, m); break;
+            default: pack_words<5>(d, cell, units, stride8, l, stage, m); break;
             }
         }
 #pragma unroll
