@@ -250,6 +250,13 @@ lbl_status lbl_label_frame_noalloc(lbl_abs_t a, const uint8_t *O, uint32_t n_pro
  * the oldest is released after a device synchronization).  Results are
  * identical to labeling each job alone.
  *
+ * Under stream capture a batch that is already kept is recorded; one that is
+ * not fails, as it would have to be laid out.  A recorded batch stays until one
+ * of its abstractions is released, and a graph that holds it may be replayed
+ * until then; up to 8 recorded batches stay at a time, the next one fails with
+ * LBL_EINVAL and leaves the capture as it was.  A replay uses the batch's
+ * buffers like a call of the same batch on hip_stream: the two must not overlap.
+ *
  * Jobs on one abstraction are placed into 64-column lane groups first-fit by
  * decreasing proposition count (a job never spans two lane groups).  With
  * the sparse layout on every abstraction, one wavefront per (word, lane

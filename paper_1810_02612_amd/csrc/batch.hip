@@ -568,11 +568,33 @@ struct BatchEntry {
     BatchBuffers bufs;
     void *dmem = nullptr;
     int device = 0;
+    bool recorded = false;  // launches recorded under stream capture point at dmem
 };
 
+// Up to kMaxEntries batches are kept, the most recent first, and besides them
+// up to kMaxRecorded that were recorded into a graph: those stay until one of
+// their abstractions is released, as nothing tells when a graph is destroyed
+// (a user object retained by the captured graph was not released with it or
+// with its executable).
 std::mutex g_entry_mu;
-std::list<std::unique_ptr<BatchEntry>> g_entries;  // most recent first
-const size_t kMaxEntries = 8;
+std::list<std::unique_ptr<BatchEntry>> g_entries;
+const size_t kMaxEntries = 8, kMaxRecorded = 8;
+
+size_t recorded_entries()
+{
+    size_t n = 0;
+    for (const auto &e : g_entries) n += e->recorded;
+    return n;
+}
+
+// Whether calls on s are being recorded into a graph.
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();  // the default stream beside another stream's capture
+    return false;
+}
 
 bool same_jobs(const std::vector<JobRef> &a, const JobRef *b, size_t n)
 {
@@ -606,7 +628,7 @@ lbl_status build_entry(BatchEntry *e)
 // The entry kept for these jobs, built for tile `want` (or for the tile
 // recorded for their shape class when want is null), moved to the front;
 // null if none.  Lock held.  Entries for the same jobs built for another
-// tile are released.
+// tile are released (but for recorded ones).
 BatchEntry *find_entry(const JobRef *jobs, size_t n_jobs, uint32_t flags, hipStream_t s, int device,
                        const BatchTile *want)
 {
@@ -620,7 +642,7 @@ BatchEntry *find_entry(const JobRef *jobs, size_t n_jobs, uint32_t flags, hipStr
                 g_entries.splice(g_entries.begin(), g_entries, it++);
                 continue;
             }
-            if (!want) {  // built for a tile no longer recorded for the class
+            if (!want && !e->recorded) {  // built for a tile no longer in use for the class
                 destroy_entry(e);
                 it = g_entries.erase(it);
                 continue;
@@ -683,12 +705,18 @@ lbl_status label_batch_cached(const JobRef *jobs, size_t n_jobs, uint32_t flags,
             destroy_entry(e.get());
             return st;
         }
-        while (g_entries.size() >= kMaxEntries) {
-            destroy_entry(g_entries.back().get());
-            g_entries.pop_back();
+        for (auto it = g_entries.end(); g_entries.size() - recorded_entries() >= kMaxEntries;) {
+            if ((*--it)->recorded) continue;
+            destroy_entry(it->get());
+            it = g_entries.erase(it);
         }
         g_entries.push_front(std::move(e));
         hit = g_entries.front().get();
+    }
+    if (!hit->recorded && capturing(s)) {
+        LBL_REQUIRE(recorded_entries() < kMaxRecorded,
+                    "too many recorded batches are kept (they are released with their abstractions)");
+        hit->recorded = true;
     }
     void *span = span_begin(s);
     const lbl_status st = enqueue_batch(hit->plan, hit->bufs, s);
