@@ -92,6 +92,9 @@ lbl_status workspace(hipStream_t s, size_t bytes, void **out);
 constexpr size_t kPinnedBytes = 4096;
 lbl_status pinned_flags(hipStream_t s, void **host);
 
+// Workgroups (of 256) of a planner sweep.
+unsigned plan_sweep_blocks(uint64_t n_product, uint64_t n_edges);
+
 // ---------------------------------------------------------------- kernels
 
 // Kernel choices (runtime representation of LBL_KERNEL_*).
