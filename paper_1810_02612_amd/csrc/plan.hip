@@ -15,9 +15,9 @@
 // predecessor graph is a tree.  A graph with n product vertices needs at most
 // n sweeps (each kernel ends; the host loop is bounded).
 //
-// A sweep reads 4 bytes of every edge and a byte per vertex; only the few
-// edges that leave a changed vertex read more.  What a call costs beyond that
-// is launches and waits, so the host does not wait between sweeps: it keeps
+// A sweep reads 13 bytes of every edge and its source's mark and distances;
+// only the few edges that leave a changed vertex read more.  What a call costs
+// beyond that is launches and waits, so the host does not wait between sweeps: it keeps
 // kAhead of them enqueued and reads in pinned memory, where each sweep reports
 // on the one before, whether that one changed anything.  The sweep after the
 // first that did not writes the outputs, the ones after it do nothing.
@@ -29,10 +29,9 @@
 // target distance, atomic minimum, about 1 us each.  An atomic for every
 // candidate instead of the check against the target's distance, which may be
 // old: 360-460 us, as the sinks' atomics go one by one.  Changed vertices as
-// bits set by atomics took up to 37 us in one sweep.  Random graphs of 100,000
-// vertices and 1,000,000 edges, 2 states: 1.93 ms, 2.02 with groups of four;
-// their edges sorted by source 1.17 and 1.80 ms.
+// bits set by atomics took up to 37 us in one sweep.  Random graphs: kLargeEdges.
 #include <algorithm>
+#include <type_traits>
 
 #include "lbl_internal.h"
 
@@ -44,6 +43,14 @@ constexpr uint64_t kNone = ~0ull;
 constexpr uint32_t kAhead = 4;    // sweeps enqueued beyond the last one reported on
 constexpr uint32_t kReports = 64; // report slots, used in turn (more than kAhead)
 constexpr uint32_t kMaxDelta = 8u << 8;
+// Edges from which k_plan_sweep's LARGE form runs.  Ms per call of random graphs
+// without and with it (and when every sweep relaxed every reached edge):
+// vertices x edges x states, unsorted 1e5 x 1e6 x 2 1.72, 1.64 (1.83); 1e6 x 4e6 x
+// 2 6.28, 4.49 (5.88); 2e6 x 6e6 x 1 8.45, 5.29 (6.52); by source 1e5 x 1e6 x 2
+// 1.40, 1.21 (1.35); 1e6 x 2e6 x 1 4.60, 3.55 (3.81); 1e6 x 4e6 x 2 4.49, 3.25
+// (3.72).  Below: 4e4 edges of 2e4 vertices 0.26, 0.29; roadmaps of 122,358 and
+// 151,916 transitions, 8 states, 0.154, 0.160 and 0.183, 0.189.
+constexpr uint64_t kLargeEdges = 3u << 18;
 
 struct Delta {
     uint8_t move[kMaxDelta];
@@ -143,7 +150,13 @@ __device__ __forceinline__ void best_min(uint64_t *best, uint64_t to, uint64_t c
 // Looks cost about 1 us each where the sources of a wavefront's edges share a
 // few cache lines (edges stored by source vertex) and far more where they
 // don't: such wavefronts look once.
-template <int S>
+//
+// LARGE (more than kLargeEdges): the edges take several turns on the chip and
+// a sweep is bound by its accesses, not by the chain.  Wavefronts whose sources lie
+// far apart read the rest only for edges of marked sources, a vertex that was
+// marked earlier in this sweep counts as marked (its edges are relaxed now and,
+// to no effect, in the next), and there are fewer looks.
+template <int S, bool LARGE>
 __global__ void __launch_bounds__(256) k_plan_sweep(PlanArgs p, uint64_t k, uint32_t most_looks)
 {
     __shared__ uint8_t moves[S << 8];
@@ -170,42 +183,59 @@ __global__ void __launch_bounds__(256) k_plan_sweep(PlanArgs p, uint64_t k, uint
     for (uint64_t i = i0; i < p.near_words; i += step) clear[i] = 0;
     __syncthreads();
     bool changed = false;
-    for (uint64_t e = i0; e < p.n_edges; e += step) {
-        const uint32_t u = p.src[e], v = p.dst[e], c = p.cost[e], sigma = p.sigma[e];
-        if (!edge_ok(p, u, v, c)) continue;
-        bool go = now[u] != 0;
-        uint32_t du[S];
+    // the product edges of edge e = (u, v) from distances du
+    auto relax = [&](uint64_t e, uint32_t v, uint32_t c, uint32_t sigma, const uint32_t (&du)[S]) {
+        uint64_t cand[S], to[S], old[S];
 #pragma unroll
-        for (int q = 0; q < S; ++q) du[q] = (uint32_t)(p.best[(uint64_t)u * p.n_states + min((uint32_t)q, p.n_states - 1)] >> 32);
-        const uint32_t looks = __ballot((uint64_t)(u - (uint32_t)__builtin_amdgcn_readfirstlane((int)u)) * p.n_states >= 128u) == 0 ? most_looks : 1u;
-        for (uint32_t r = 1;; ++r) {
-            if (go) {
-                uint64_t cand[S], to[S], old[S];
+        for (int q = 0; q < S; ++q) {
+            const uint32_t q2 = (uint32_t)q < p.n_states ? moves[((uint32_t)q << p.n_props) | sigma] : p.n_states;
+            const uint64_t nd = (uint64_t)du[q] + c;
+            to[q] = (uint64_t)v * p.n_states + min(q2, p.n_states - 1);
+            // no product edge: the source is not reached, the monitor
+            // rejects, the cost cannot be represented, or it ends at the
+            // start, which keeps distance 0 and no predecessor
+            const bool edge = du[q] != kInf && q2 < p.n_states && nd < kInf && to[q] != p.start;
+            cand[q] = edge ? (nd << 32) | (e * p.n_states + q) : kNone;
+            old[q] = p.best[to[q]];
+        }
+        bool nearer = false;
 #pragma unroll
-                for (int q = 0; q < S; ++q) {
-                    const uint32_t q2 = (uint32_t)q < p.n_states ? moves[((uint32_t)q << p.n_props) | sigma] : p.n_states;
-                    const uint64_t nd = (uint64_t)du[q] + c;
-                    to[q] = (uint64_t)v * p.n_states + min(q2, p.n_states - 1);
-                    // no product edge: the source is not reached, the monitor
-                    // rejects, the cost cannot be represented, or it ends at the
-                    // start, which keeps distance 0 and no predecessor
-                    const bool edge = du[q] != kInf && q2 < p.n_states && nd < kInf && to[q] != p.start;
-                    cand[q] = edge ? (nd << 32) | (e * p.n_states + q) : kNone;
-                    old[q] = p.best[to[q]];
-                }
-                bool nearer = false;
-#pragma unroll
-                for (int q = 0; q < S; ++q)
-                    if (cand[q] < old[q]) {  // values only decrease: otherwise it cannot win
-                        best_min(p.best, to[q], cand[q]);
-                        // a smaller edge id at the same distance changes no neighbour
-                        nearer = nearer || cand[q] >> 32 < old[q] >> 32;
-                    }
-                if (nearer) {
-                    changed = true;
-                    next[v] = 1;
-                }
+        for (int q = 0; q < S; ++q)
+            if (cand[q] < old[q]) {  // values only decrease: otherwise it cannot win
+                best_min(p.best, to[q], cand[q]);
+                // a smaller edge id at the same distance changes no neighbour
+                nearer = nearer || cand[q] >> 32 < old[q] >> 32;
             }
+        if (nearer) {
+            changed = true;
+            next[v] = 1;
+        }
+    };
+    for (uint64_t e = i0; e < p.n_edges; e += step) {
+        const uint32_t u = p.src[e];
+        auto read_source = [&](uint32_t (&du)[S]) {
+#pragma unroll
+            for (int q = 0; q < S; ++q) du[q] = (uint32_t)(p.best[(uint64_t)u * p.n_states + min((uint32_t)q, p.n_states - 1)] >> 32);
+        };
+        // whether the sources of the wavefront's edges lie far apart
+        auto far = [&] { return __ballot((uint64_t)(u - (uint32_t)__builtin_amdgcn_readfirstlane((int)u)) * p.n_states >= 128u) != 0; };
+        uint32_t du[S];
+        if constexpr (LARGE) {
+            if (far()) {
+                if (u >= p.n_vertices || (now[u] | next[u]) == 0) continue;
+                const uint32_t v = p.dst[e], c = p.cost[e], sigma = p.sigma[e];
+                read_source(du);
+                if (edge_ok(p, u, v, c)) relax(e, v, c, sigma, du);
+                continue;
+            }
+        }
+        const uint32_t v = p.dst[e], c = p.cost[e], sigma = p.sigma[e];
+        if (!edge_ok(p, u, v, c)) continue;
+        bool go = (LARGE ? now[u] | next[u] : now[u]) != 0;
+        read_source(du);
+        const uint32_t looks = far() ? 1u : most_looks;
+        for (uint32_t r = 1;; ++r) {
+            if (go) relax(e, v, c, sigma, du);
             if (r >= looks) break;
             // the source again, as the other workgroups have left it by now
             go = false;
@@ -310,10 +340,14 @@ extern "C" lbl_status lbl_product_shortest_paths(uint64_t n_vertices, uint64_t n
     bool done = false;
     uint32_t idle = 0;
     const dim3 grid(plan_sweep_blocks(n, n_edges));
-    // a look reads n_states distances per edge; with more edges than the chip
-    // holds threads, later edges wait for the looks of earlier ones
-    const uint32_t looks = std::min(n_edges > (1u << 21) ? 8u : 16u, std::max(4u, 32u / n_states));
-    const auto sweep = n_states <= 1 ? k_plan_sweep<1> : n_states <= 2 ? k_plan_sweep<2> : n_states <= 4 ? k_plan_sweep<4> : k_plan_sweep<8>;
+    // a look reads n_states distances per edge
+    const bool large = n_edges > kLargeEdges;
+    const uint32_t looks = large ? 4u : std::min(16u, std::max(4u, 32u / n_states));
+    auto of = [large](auto s) { return large ? &k_plan_sweep<s.value, true> : &k_plan_sweep<s.value, false>; };
+    const auto sweep = n_states <= 1   ? of(std::integral_constant<int, 1>())
+                       : n_states <= 2 ? of(std::integral_constant<int, 2>())
+                       : n_states <= 4 ? of(std::integral_constant<int, 4>())
+                                       : of(std::integral_constant<int, 8>());
     while (!done && known <= n) {
         if (launched < known + 1 + kAhead && launched < n + 2) {
             hipLaunchKernelGGL(sweep, grid, dim3(256), 0, s, p, launched, looks);
