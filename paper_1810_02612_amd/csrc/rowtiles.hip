@@ -141,15 +141,26 @@ __device__ __forceinline__ uint32_t or8(uint32_t v)
 // The word masks of a group of 8 lanes, whose lane y holds 8 consecutive
 // cells of the word at src (row y of its 8 x 8 block, or with z-order ids its
 // cells 8y ..), P bytes each: mask[p] has a bit for every cell whose byte p is
-// not zero.
-template <uint32_t P>
+// not zero.  The cells start at a multiple of 8 bytes from O.  SHIFT: O is not
+// dword aligned; the lane reads the 2 P + 1 aligned dwords its cells touch and
+// shifts their bits (loads of these lengths from odd addresses made 100,000
+// random rows x 128^2, 256 words to a tile, take 36.1 us with 4 propositions and
+// 21.2 with 2; so 20.0 and 14.9, dword aligned 18.1 and 12.3; the split of
+// sparse.hip 18.7 and 16.3).
+template <uint32_t P, bool SHIFT>
 __device__ __forceinline__ void word_masks(const uint8_t *src, uint32_t y, uint32_t morton, uint64_t (&mask)[P])
 {
-    uint32_t d[2 * P];
-    __builtin_memcpy(d, src, 8 * P);
+    const uint32_t mis = SHIFT ? (uint32_t)(reinterpret_cast<uintptr_t>(src) & 3u) : 0u;  // 1 .. 3 if SHIFT
+    constexpr uint32_t N = 2 * P + (SHIFT ? 1 : 0);
+    uint32_t d[N];
+    __builtin_memcpy(d, __builtin_assume_aligned(src - mis, 4), 4 * N);
     uint32_t bits = 0;  // bit P x + p: byte p of cell x
 #pragma unroll
     for (uint32_t k = 0; k < 2 * P; ++k) bits |= nz_bytes(d[k]) << (4 * k);
+    if constexpr (SHIFT) {
+        const uint32_t last = nz_bytes(d[2 * P]);
+        bits = P == 4 ? __builtin_amdgcn_alignbit(last, bits, mis) : (bits | last << (8 * (P & 3u))) >> mis;
+    }
 #pragma unroll
     for (uint32_t p = 0; p < P; ++p) {
         uint32_t lo = 0, hi = 0;
@@ -174,7 +185,7 @@ __device__ __forceinline__ void word_masks(const uint8_t *src, uint32_t y, uint3
 }
 
 // One workgroup per tile: masks of the tile's words into LDS (eight lanes per
-// word, each reading a row of its cells), then the tile's chunks of 64 entries dealt to
+// word, each reading a row of its cells), then the tile's chunks of 128 entries dealt to
 // the wavefronts in turn, each lane ORing its entry's label into its row's
 // LDS accumulator, then the rows' label bytes.
 //
@@ -190,7 +201,7 @@ __device__ __forceinline__ void word_masks(const uint8_t *src, uint32_t y, uint3
 constexpr int kRowWaves = 8;
 constexpr int kRowAhead = 3;
 
-template <uint32_t P>
+template <uint32_t P, bool SHIFT>
 __global__ void __launch_bounds__(64 * kRowWaves, 8)
 k_label_row_tiles(const RowTile *__restrict__ tiles, const RowChunk *__restrict__ chunks,
                   const uint32_t *__restrict__ seg_cell, const uint8_t *__restrict__ rows,
@@ -227,7 +238,7 @@ k_label_row_tiles(const RowTile *__restrict__ tiles, const RowChunk *__restrict_
         const uint64_t off = morton ? 8u * y : (uint64_t)y * nx;
         for (uint32_t i = threadIdx.x / 8; i < t.n_seg; i += 8 * kRowWaves) {  // whole groups of lanes
             uint64_t m[P];
-            word_masks<P>(O + (seg_cell[t.seg_first + i] + off) * P, y, morton, m);
+            word_masks<P, SHIFT>(O + (seg_cell[t.seg_first + i] + off) * P, y, morton, m);
 #pragma unroll
             for (uint32_t p = 0; p < P; ++p)
                 if (y == p) msk[i * P + p] = m[p];
@@ -274,7 +285,8 @@ k_label_row_tiles(const RowTile *__restrict__ tiles, const RowChunk *__restrict_
 template <uint32_t P>
 hipError_t launch(const lbl_abs *a, const RowTiles &t, const uint8_t *O, uint8_t *L, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_label_row_tiles<P>, dim3(t.n_tiles), dim3(64 * kRowWaves), (size_t)t.max_seg * P * sizeof(uint64_t),
+    const auto kernel = reinterpret_cast<uintptr_t>(O) & 3u ? &k_label_row_tiles<P, true> : &k_label_row_tiles<P, false>;
+    hipLaunchKernelGGL(kernel, dim3(t.n_tiles), dim3(64 * kRowWaves), (size_t)t.max_seg * P * sizeof(uint64_t),
                        s, t.tiles, t.chunks, t.seg_cell, t.row, t.val, O, a->nx, (uint32_t)a->order.morton,
                        t.rows_per_tile, a->n_traj, L);
     return hipGetLastError();
