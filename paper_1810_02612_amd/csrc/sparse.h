@@ -246,7 +246,7 @@ std::vector<double> run_costs(const std::vector<uint64_t> &start, const std::vec
 // n_props bytes again.  aligned: cells start at multiples of 4 bytes.
 bool tiles_pack(uint64_t n_seg, uint32_t n_props, bool aligned);
 // Whether a frame whose tiles do is labeled by one workgroup, in one launch.
-bool one_launch_pays(uint64_t n_ent, uint64_t n_seg, uint32_t n_rb, uint32_t n_props);
+bool one_launch_pays(uint64_t n_ent, uint64_t n_seg, uint32_t n_rb, uint32_t n_props, bool aligned);
 // Whether a layout of nnz words that take n_ent run entries is labeled by the
 // run kernels.
 bool use_runs(uint64_t nnz, uint64_t n_ent);

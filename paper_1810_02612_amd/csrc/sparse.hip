@@ -2188,15 +2188,25 @@ lbl_status sparse_part(const uint64_t *T, uint32_t row_stride, uint64_t n_rows, 
     return LBL_OK;
 }
 
-// One workgroup walks all rounds, some 64 entries each, and builds every
-// segment's tables; two launches cost 3 to 4 us more than one.  Us per frame
-// with two launches and one, rounds + segments x pieces / 2 in brackets: 1,000 x
-// 64^2 x 8 12.2, 8.6 (182); x 64 12.6, 11.3 (246); 2,000 x 64^2 x 8 11.9, 9.0
-// (299); 4,000 x 64^2 x 12 12.1, 15.7 (530); 2,000 x 128^2 x 40 12.3, 21.8 (800).
-bool one_launch_pays(uint64_t n_ent, uint64_t n_seg, uint32_t n_rb, uint32_t n_props)
+// One workgroup walks all rounds (one per 64 entries, and one per segment whose
+// tables it builds); two launches cost 2.5 us of host time more than one, back to
+// back 10.1 us per frame whatever the size.  Us per frame with one launch, rounds
+// and segments in brackets.  32-bit masks: 1,000 x 64^2 x 8 7.7 (118, 64); 64 x 96
+// x 24 8.2 (87, 96); 72 x 64 x 12 9.4 (193, 72); 64 x 96 x 8 8.6 (203, 96); 128^2 x
+// 16 11.4 (162, 256); 200 x 104 x 16 13.3 (102, 325).  64-bit masks, whose cells take
+// three or four loads: 72 x 64 x 40 9.1 (83, 72); 64^2 x 36 9.2 (116, 64), 11.2
+// (178, 64); 64 x 96 x 36 9.9 (79, 96); 72 x 64 x 48 10.3 (149, 72); 64^2 x 52 10.1 (104, 64); 64 x 96 x 64 10.2
+// (56, 96); 72 x 64 x 64 13.3 (161, 72).  Where cells are not dword aligned every
+// round's loads cost, built or not: 64 x 96 x 10 7.6 (47, 96); 64 x 96 x 14 11.7
+// (193, 96); 72 x 64 x 17 9.0 (25, 72); 64^2 x 26 10.7 (94, 64); 72 x 64 x 26 12.9
+// (141, 72); 64^2 x 41 15.8 (60, 64), x 61 29.1 (144, 64).
+bool one_launch_pays(uint64_t n_ent, uint64_t n_seg, uint32_t n_rb, uint32_t n_props, bool aligned)
 {
-    const uint64_t pieces = n_props < 16 ? 2 : (n_props + 15) / 16;
-    return n_rb == 1 && n_ent / 64 + n_seg * pieces / 2 <= 320;
+    const uint64_t rounds = n_ent / 64, pieces = (n_props + 15) / 16;
+    if (n_rb != 1) return false;
+    if (!aligned) return n_props <= 32 && rounds + n_seg <= (n_props < 16 ? 200 : 140);
+    if (n_props <= 32) return 2 * rounds + 5 * n_seg <= 900;
+    return 5 * rounds + 3 * n_seg * pieces <= 1400;
 }
 
 // A segment costs a cache access per lane and piece loaded (more where pieces
@@ -2484,11 +2494,12 @@ lbl_status run_swm_t(const lbl_abs *a, const SpTiling &tl, const uint8_t *O, uin
         if (spans) lbl::span_end(b, st, kind);
     };
     const dim3 pack_grid((unsigned)(((uint64_t)sp.n_used * 64 + 255) / 256));
+    const bool aligned = n_props % 4 == 0 && reinterpret_cast<uintptr_t>(O) % 4 == 0;
     const bool from_frame = sp.ent && n_props >= 4 && (sizeof(M) == 4 || n_props > 32) &&  // what for_pieces covers
                             8ull * a->nx * n_props < (1ull << 31) &&                       // 32-bit offsets
-                            tiles_pack(sp.n_segments, n_props, n_props % 4 == 0 && reinterpret_cast<uintptr_t>(O) % 4 == 0);
+                            tiles_pack(sp.n_segments, n_props, aligned);
     void *spn = nullptr;
-    if (from_frame && one_launch_pays(sp.n_ent, sp.n_segments, sp.n_rb, n_props)) {
+    if (from_frame && one_launch_pays(sp.n_ent, sp.n_segments, sp.n_rb, n_props, aligned)) {
         const SpTiling &one = sp.tilings[1];  // one tile per row block
         spn = span_begin(s);
         hipLaunchKernelGGL(label_runs_whole<M>(n_props), dim3(sp.n_rb), dim3(64 * kTileWaves),

@@ -28,9 +28,29 @@ static void plan_blocks()
         }
 }
 
+// One launch for the smallest frames only, by mask width and alignment: (entries,
+// segments, propositions, aligned) where it measured faster and slower than two.
+static void one_launch()
+{
+    struct Case {
+        uint64_t n_ent, n_seg;
+        uint32_t n_props;
+        bool aligned, pays;
+    };
+    for (const Case &c : {Case{7600, 64, 8, true, true}, Case{5612, 96, 24, true, true}, Case{12994, 96, 8, true, true},
+                          Case{6562, 325, 16, true, false}, Case{5345, 72, 40, true, true}, Case{7441, 64, 36, true, true},
+                          Case{10324, 72, 64, true, false}, Case{11417, 64, 36, true, false}, Case{2988, 96, 10, false, true},
+                          Case{12348, 96, 14, false, false}, Case{1595, 72, 17, false, true}, Case{6041, 64, 26, false, false},
+                          Case{3811, 64, 41, false, false}, Case{9186, 64, 61, false, false}, Case{64, 1, 33, false, false}}) {
+        CHECK(one_launch_pays(c.n_ent, c.n_seg, 1, c.n_props, c.aligned) == c.pays);
+        CHECK(!one_launch_pays(c.n_ent, c.n_seg, 2, c.n_props, c.aligned));
+    }
+}
+
 int main()
 {
     plan_blocks();
+    one_launch();
     if (fails) return 1;
     std::printf("rules OK\n");
     return 0;
