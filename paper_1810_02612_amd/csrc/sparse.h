@@ -243,8 +243,9 @@ void make_run_tiling(const std::vector<uint64_t> &start, const std::vector<uint3
 std::vector<double> run_costs(const std::vector<uint64_t> &start, const std::vector<uint64_t> &rb_seg);
 // Whether one frame's tiles form their words' cell masks from O themselves,
 // instead of a pack kernel: each of n_seg segments reads its word's 64 cells of
-// n_props bytes again.  aligned: cells start at multiples of 4 bytes.
-bool tiles_pack(uint64_t n_seg, uint32_t n_props, bool aligned);
+// n_props bytes again, and each round of the n_ent run entries one cell.
+// aligned: cells start at multiples of 4 bytes.
+bool tiles_pack(uint64_t n_ent, uint64_t n_seg, uint32_t n_props, bool aligned);
 // Whether a frame whose tiles do is labeled by one workgroup, in one launch.
 bool one_launch_pays(uint64_t n_ent, uint64_t n_seg, uint32_t n_rb, uint32_t n_props, bool aligned);
 // Whether a layout of nnz words that take n_ent run entries is labeled by the

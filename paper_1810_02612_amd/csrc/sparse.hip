@@ -2217,10 +2217,16 @@ bool one_launch_pays(uint64_t n_ent, uint64_t n_seg, uint32_t n_rb, uint32_t n_p
 // 25,000 x 512^2 x 40 17.3, 15.6 (48k); 120,000 x 256^2 x 64 19.1, 21.4 (60k);
 // 57,000 x 512^2 x 64 21.5, 22.5 (112k).  Unaligned: 40,000 x 256^2 x 17 15.0,
 // 16.0 (10k); 12,452 x 96 x 312 x 34 14.0, 11.9 (3k); 120,000 x 256^2 x 17 16.6, 22.4 (30k); 75,003 x 328^2 x 37 17.2,
-// 21.2 (50k).
-bool tiles_pack(uint64_t n_seg, uint32_t n_props, bool aligned)
+// 21.2 (50k).  A round that builds no tables loads the pieces of one cell all the
+// same, which costs where a 16-byte piece lies off dword alignment; with the pack
+// kernel and without, rounds x pieces in brackets: 27,710 x 64^2 x 31 12.5, 10.4
+// (5.7k); 34,551 x 64^2 x 22 13.5, 11.7 (7.8k); 70,632 x 64 x 96 x 30 12.5, 12.4 (11k);
+// 52,439 x 64^2 x 31 13.9, 14.7 (13k); 26,929 x 64^2 x 33 13.2, 12.9 (9.3k); 22,607 x
+// 64^2 x 42 14.4, 16.5 (9.7k); 49,860 x 72 x 64 x 59 13.1, 15.9 (19k).
+bool tiles_pack(uint64_t n_ent, uint64_t n_seg, uint32_t n_props, bool aligned)
 {
     const uint64_t pieces = n_props < 16 ? 2 : (n_props + 15) / 16;
+    if (!aligned && n_props >= 16 && n_ent / 64 * pieces > (n_props <= 32 ? 12500 : 9500)) return false;
     return n_seg <= (1ull << 32) && n_seg * pieces * (aligned ? 1 : 16) <= 50000;
 }
 
@@ -2497,7 +2503,7 @@ lbl_status run_swm_t(const lbl_abs *a, const SpTiling &tl, const uint8_t *O, uin
     const bool aligned = n_props % 4 == 0 && reinterpret_cast<uintptr_t>(O) % 4 == 0;
     const bool from_frame = sp.ent && n_props >= 4 && (sizeof(M) == 4 || n_props > 32) &&  // what for_pieces covers
                             8ull * a->nx * n_props < (1ull << 31) &&                       // 32-bit offsets
-                            tiles_pack(sp.n_segments, n_props, aligned);
+                            tiles_pack(sp.n_ent, sp.n_segments, n_props, aligned);
     void *spn = nullptr;
     if (from_frame && one_launch_pays(sp.n_ent, sp.n_segments, sp.n_rb, n_props, aligned)) {
         const SpTiling &one = sp.tilings[1];  // one tile per row block
