@@ -47,8 +47,8 @@ constexpr uint32_t kMaxDelta = 8u << 8;
 // without and with it (and when every sweep relaxed every reached edge):
 // vertices x edges x states, unsorted 1e5 x 1e6 x 2 1.72, 1.64 (1.83); 1e6 x 4e6 x
 // 2 6.28, 4.49 (5.88); 2e6 x 6e6 x 1 8.45, 5.29 (6.52); by source 1e5 x 1e6 x 2
-// 1.40, 1.21 (1.35); 1e6 x 2e6 x 1 4.60, 3.55 (3.81); 1e6 x 4e6 x 2 4.49, 3.25
-// (3.72).  Below: 4e4 edges of 2e4 vertices 0.26, 0.29; roadmaps of 122,358 and
+// 1.41, 1.21 (1.35); 1e6 x 2e6 x 1 4.58, 3.61 (3.92); 1e6 x 4e6 x 2 4.54, 3.27
+// (3.79).  Below: 4e4 edges of 2e4 vertices 0.26, 0.29; roadmaps of 122,358 and
 // 151,916 transitions, 8 states, 0.154, 0.160 and 0.183, 0.189.
 constexpr uint64_t kLargeEdges = 3u << 18;
 
@@ -183,59 +183,47 @@ __global__ void __launch_bounds__(256) k_plan_sweep(PlanArgs p, uint64_t k, uint
     for (uint64_t i = i0; i < p.near_words; i += step) clear[i] = 0;
     __syncthreads();
     bool changed = false;
-    // the product edges of edge e = (u, v) from distances du
-    auto relax = [&](uint64_t e, uint32_t v, uint32_t c, uint32_t sigma, const uint32_t (&du)[S]) {
-        uint64_t cand[S], to[S], old[S];
-#pragma unroll
-        for (int q = 0; q < S; ++q) {
-            const uint32_t q2 = (uint32_t)q < p.n_states ? moves[((uint32_t)q << p.n_props) | sigma] : p.n_states;
-            const uint64_t nd = (uint64_t)du[q] + c;
-            to[q] = (uint64_t)v * p.n_states + min(q2, p.n_states - 1);
-            // no product edge: the source is not reached, the monitor
-            // rejects, the cost cannot be represented, or it ends at the
-            // start, which keeps distance 0 and no predecessor
-            const bool edge = du[q] != kInf && q2 < p.n_states && nd < kInf && to[q] != p.start;
-            cand[q] = edge ? (nd << 32) | (e * p.n_states + q) : kNone;
-            old[q] = p.best[to[q]];
-        }
-        bool nearer = false;
-#pragma unroll
-        for (int q = 0; q < S; ++q)
-            if (cand[q] < old[q]) {  // values only decrease: otherwise it cannot win
-                best_min(p.best, to[q], cand[q]);
-                // a smaller edge id at the same distance changes no neighbour
-                nearer = nearer || cand[q] >> 32 < old[q] >> 32;
-            }
-        if (nearer) {
-            changed = true;
-            next[v] = 1;
-        }
-    };
     for (uint64_t e = i0; e < p.n_edges; e += step) {
         const uint32_t u = p.src[e];
-        auto read_source = [&](uint32_t (&du)[S]) {
-#pragma unroll
-            for (int q = 0; q < S; ++q) du[q] = (uint32_t)(p.best[(uint64_t)u * p.n_states + min((uint32_t)q, p.n_states - 1)] >> 32);
-        };
+        auto marked = [&] { return (LARGE ? now[u] | next[u] : now[u]) != 0; };
         // whether the sources of the wavefront's edges lie far apart
         auto far = [&] { return __ballot((uint64_t)(u - (uint32_t)__builtin_amdgcn_readfirstlane((int)u)) * p.n_states >= 128u) != 0; };
-        uint32_t du[S];
-        if constexpr (LARGE) {
-            if (far()) {
-                if (u >= p.n_vertices || (now[u] | next[u]) == 0) continue;
-                const uint32_t v = p.dst[e], c = p.cost[e], sigma = p.sigma[e];
-                read_source(du);
-                if (edge_ok(p, u, v, c)) relax(e, v, c, sigma, du);
-                continue;
-            }
-        }
+        if (LARGE && far() && (u >= p.n_vertices || !marked())) continue;
         const uint32_t v = p.dst[e], c = p.cost[e], sigma = p.sigma[e];
         if (!edge_ok(p, u, v, c)) continue;
-        bool go = (LARGE ? now[u] | next[u] : now[u]) != 0;
-        read_source(du);
+        bool go = marked();
+        uint32_t du[S];
+#pragma unroll
+        for (int q = 0; q < S; ++q) du[q] = (uint32_t)(p.best[(uint64_t)u * p.n_states + min((uint32_t)q, p.n_states - 1)] >> 32);
         const uint32_t looks = far() ? 1u : most_looks;
         for (uint32_t r = 1;; ++r) {
-            if (go) relax(e, v, c, sigma, du);
+            if (go) {
+                uint64_t cand[S], to[S], old[S];
+#pragma unroll
+                for (int q = 0; q < S; ++q) {
+                    const uint32_t q2 = (uint32_t)q < p.n_states ? moves[((uint32_t)q << p.n_props) | sigma] : p.n_states;
+                    const uint64_t nd = (uint64_t)du[q] + c;
+                    to[q] = (uint64_t)v * p.n_states + min(q2, p.n_states - 1);
+                    // no product edge: the source is not reached, the monitor
+                    // rejects, the cost cannot be represented, or it ends at the
+                    // start, which keeps distance 0 and no predecessor
+                    const bool edge = du[q] != kInf && q2 < p.n_states && nd < kInf && to[q] != p.start;
+                    cand[q] = edge ? (nd << 32) | (e * p.n_states + q) : kNone;
+                    old[q] = p.best[to[q]];
+                }
+                bool nearer = false;
+#pragma unroll
+                for (int q = 0; q < S; ++q)
+                    if (cand[q] < old[q]) {  // values only decrease: otherwise it cannot win
+                        best_min(p.best, to[q], cand[q]);
+                        // a smaller edge id at the same distance changes no neighbour
+                        nearer = nearer || cand[q] >> 32 < old[q] >> 32;
+                    }
+                if (nearer) {
+                    changed = true;
+                    next[v] = 1;
+                }
+            }
             if (r >= looks) break;
             // the source again, as the other workgroups have left it by now
             go = false;
