@@ -127,7 +127,12 @@ typedef struct {
  * With LBL_LOAD_SPARSE_ONLY the device holds only the sparse tiled layout
  * (non-zero 64-cell words of T, 10 bytes each, and its tilings): a workspace
  * of 2^21 cells and a million rows, 288 GB as bitpacked rows, takes about a
- * gigabyte.  Labels are identical to those of a full load.
+ * gigabyte.  Labels are identical to those of a full load.  The layout keeps
+ * further forms of the words that make frames faster (8 bytes a word, 9.4
+ * where neighbouring rows meet the same words, or both and then not the 10:
+ * 17 to 19 bytes a word) where 22 bytes a word are at most a sixteenth of the
+ * device memory free at load and can be allocated; without them labels are
+ * the same.
  *
  * Errors: LBL_EINVAL for a null pointer, n_traj == 0, nx or ny not a positive
  * multiple of 8, an unknown cell_order or LBL_MORTON on a grid that is not a

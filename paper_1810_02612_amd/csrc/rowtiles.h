@@ -58,7 +58,7 @@ bool row_tiles_pay(uint64_t nnz, uint64_t n_seg, uint32_t max_seg);
 
 // The row tiles of a's sparse layout (sp's entries still in row and val), or
 // null where they do not pay.
-lbl_status build_row_tiles(lbl_abs *a, const SparseLayout &sp, const std::vector<uint64_t> &seg_start,
+lbl_status build_row_tiles(const lbl_abs *a, const SparseLayout &sp, const std::vector<uint64_t> &seg_start,
                            const std::vector<uint32_t> &seg_word, const std::vector<uint64_t> &rb_seg,
                            std::unique_ptr<RowTiles> *out);
 

@@ -324,7 +324,7 @@ bool row_tiles_pay(uint64_t nnz, uint64_t n_seg, uint32_t max_seg)
     return nnz != 0 && ((n_seg <= nnz / 16 && max_seg <= kRowTileSegs) || (n_seg <= (1u << 17) && max_seg <= 384));
 }
 
-lbl_status build_row_tiles(lbl_abs *a, const SparseLayout &sp, const std::vector<uint64_t> &seg_start,
+lbl_status build_row_tiles(const lbl_abs *a, const SparseLayout &sp, const std::vector<uint64_t> &seg_start,
                            const std::vector<uint32_t> &seg_word, const std::vector<uint64_t> &rb_seg,
                            std::unique_ptr<RowTiles> *out)
 {

@@ -168,6 +168,7 @@ struct SparseLayout {
     DirectLayout direct;
     std::unique_ptr<RowTiles> row_tiles;
     size_t round_bytes = 0;      // device bytes of all tilings' tables
+    void drop_tiles();           // releases everything over the words
     ~SparseLayout();
 };
 
@@ -248,6 +249,23 @@ std::vector<double> run_costs(const std::vector<uint64_t> &start, const std::vec
 bool tiles_pack(uint64_t n_ent, uint64_t n_seg, uint32_t n_props, bool aligned);
 // Whether a frame whose tiles do is labeled by one workgroup, in one launch.
 bool one_launch_pays(uint64_t n_ent, uint64_t n_seg, uint32_t n_rb, uint32_t n_props, bool aligned);
+// Whether the copies of a layout's nnz words that make frames faster (run
+// entries and row tiles) may be made with so many bytes of the device free.
+bool copies_fit(uint64_t nnz, size_t free_bytes);
+// Clears this thread's message and the runtime's last error.
+void forget_errors();
+// make(copies): with copies first, and where these fail for want of memory or of
+// 32-bit offsets (their tilings span up to a quarter more entries) without.
+template <typename Make>
+lbl_status with_copies(bool copies, Make make)
+{
+    if (copies) {
+        const lbl_status st = make(true);
+        if (st != LBL_ENOMEM && st != LBL_EINVAL) return st;
+        forget_errors();
+    }
+    return make(false);
+}
 // Whether a layout of nnz words that take n_ent run entries is labeled by the
 // run kernels.
 bool use_runs(uint64_t nnz, uint64_t n_ent);

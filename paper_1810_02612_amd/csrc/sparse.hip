@@ -52,6 +52,7 @@
 // nor the split into tiles changes the result.  No global atomics are used.
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <queue>
 #include <type_traits>
 
@@ -1990,11 +1991,18 @@ void make_direct(const std::vector<uint64_t> &seg_start, const std::vector<uint6
 
 SparseLayout::~SparseLayout()
 {
+    drop_tiles();
     (void)hipFree(row);
     (void)hipFree(val);
-    (void)hipFree(ent);
     (void)hipFree(used_words);
     (void)hipFree(pack_first);
+}
+
+void SparseLayout::drop_tiles()
+{
+    (void)hipFree(ent);
+    ent = nullptr;
+    n_ent = 0;
     for (SpTiling &t : tilings) {
         (void)hipFree(t.tasks);
         (void)hipFree(t.rounds);
@@ -2010,6 +2018,10 @@ SparseLayout::~SparseLayout()
     (void)hipFree(direct.parts);
     (void)hipFree(direct.chunks);
     (void)hipFree(direct.seg_word);
+    tilings.clear();
+    direct = DirectLayout{};
+    row_tiles.reset();
+    round_bytes = 0;
 }
 
 void free_sparse(SparseLayout *sp) { delete sp; }
@@ -2276,6 +2288,85 @@ static lbl_status make_runs(SparseLayout *sp, const std::vector<uint64_t> &seg_s
     return LBL_OK;
 }
 
+// Run entries and row tiles are copies of the words, 8 and about 9.4 bytes a
+// word beside their 10 (2 more while the tilings are made), that only make
+// frames faster.  An abstraction near the device's memory does without: they
+// may take a sixteenth of what is free.
+bool copies_fit(uint64_t nnz, size_t free_bytes) { return nnz * 22 <= free_bytes / 16; }
+
+void forget_errors()
+{
+    clear_error();
+    (void)hipGetLastError();
+}
+
+// The tilings and other tables over sp's words; copies: run entries and row
+// tiles too, where they are the faster form.
+static lbl_status lay_out(const lbl_abs *a, SparseLayout *sp, const std::vector<uint64_t> &seg_start,
+                          const std::vector<uint32_t> &seg_word, const std::vector<uint64_t> &rb_seg, bool copies)
+{
+    sp->drop_tiles();
+    const uint64_t nnz = sp->nnz;
+    const uint32_t n_cu = (uint32_t)device_cu_count();
+    sp->tilings.resize(kNarrowTiling + 1);
+    std::vector<uint16_t> rows_host(nnz);
+    std::vector<uint64_t> run_start;
+    if (copies) {
+        const lbl_status st = make_runs(sp, seg_start, &run_start, &rows_host);
+        if (st != LBL_OK) return st;
+    }
+    const bool runs = sp->ent != nullptr;
+    if (!runs && nnz)
+        LBL_HIP_TRY(hipMemcpy(rows_host.data(), sp->row, nnz * sizeof(uint16_t), hipMemcpyDeviceToHost));
+    const std::vector<uint64_t> &tile_start = runs ? run_start : seg_start;
+    const std::vector<double> costs = (runs ? run_costs : block_costs)(tile_start, rb_seg);
+    for (int i = 0; i <= kNarrowTiling; ++i) {
+        // the 32-bit mask kernel runs two tile workgroups per CU
+        const bool one_frame = i == 0 || i == kNarrowTiling;
+        std::vector<uint32_t> k = one_frame ? choose_tiles(costs, i == 0 ? n_cu : 2 * n_cu)
+                                            : std::vector<uint32_t>(sp->n_rb, 1u << (i - 1));
+        TilingHost h;
+        (runs ? make_run_tiling : make_tiling)(tile_start, seg_word, rb_seg, k, &h);
+        if (runs)
+            for (SpRound &r : h.rounds)
+                r.tcell = a->order.morton ? r.tword * 64u : a->order.word_cell[(uint64_t)r.tword * 64];
+        // the tile kernels address a task's entries (8 bytes each) and round
+        // records with 32-bit byte offsets
+        for (const SpTask &t : h.tasks)
+            LBL_REQUIRE((uint64_t)t.n_rounds * sizeof(SpRound) < (1ull << 32) &&
+                            (t.n_rounds == 0 || (uint64_t)h.rounds[t.round0 + t.n_rounds - 1].e_off + 64 < (1ull << 29)),
+                        "a tile task spans more entries than the tile kernels address");
+        lbl_status st = upload_tiling(h, &sp->tilings[i], &sp->round_bytes);
+        if (st != LBL_OK) return st;
+        CompactHost c;
+        if (make_compact(h, rows_host, tile_start, rb_seg, a->n_traj, &c)) {
+            st = upload_compact(c, &sp->tilings[i], &sp->round_bytes);
+            if (st != LBL_OK) return st;
+        }
+    }
+    if (copies) {
+        const lbl_status st = build_row_tiles(a, *sp, seg_start, seg_word, rb_seg, &sp->row_tiles);
+        if (st != LBL_OK) return st;
+        if (sp->row_tiles) sp->round_bytes += sp->row_tiles->bytes();
+    }
+    // the direct-mask kernel's tiles: two workgroups per CU
+    DirectHost dh;
+    make_direct(seg_start, rb_seg, 2 * n_cu, &dh);
+    const lbl_status st = upload_direct(dh, seg_word, !sp->row_tiles, &sp->direct, &sp->round_bytes);
+    if (st != LBL_OK) return st;
+    if (copies && getenv("LBL_FAULT_LAYOUT")) {
+        set_error("injected layout failure");
+        return LBL_ENOMEM;
+    }
+    if (runs && sp->row_tiles) {  // no kernel reads the words in this order then
+        (void)hipFree(sp->row);
+        (void)hipFree(sp->val);
+        sp->row = nullptr;
+        sp->val = nullptr;
+    }
+    return LBL_OK;
+}
+
 lbl_status sparse_assemble(lbl_abs *a, std::vector<SparsePart> &parts)
 {
     const uint32_t W = a->n_words;
@@ -2373,62 +2464,12 @@ lbl_status sparse_assemble(lbl_abs *a, std::vector<SparsePart> &parts)
         for (const void *f : {reinterpret_cast<const void *>(label_runs_frame<uint64_t>(np)),
                               reinterpret_cast<const void *>(label_runs_whole<uint64_t>(np))})
             LBL_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRunLds));
-    const uint32_t n_cu = (uint32_t)device_cu_count();
-    sp->tilings.resize(kNarrowTiling + 1);
-    std::vector<uint16_t> rows_host(nnz);
-    std::vector<uint64_t> run_start;
-    {
-        const lbl_status st = make_runs(sp.get(), seg_start, &run_start, &rows_host);
-        if (st != LBL_OK) return st;
-    }
-    const bool runs = sp->ent != nullptr;
-    if (!runs && nnz)
-        LBL_HIP_TRY(hipMemcpy(rows_host.data(), sp->row, nnz * sizeof(uint16_t), hipMemcpyDeviceToHost));
-    const std::vector<uint64_t> &tile_start = runs ? run_start : seg_start;
-    const std::vector<double> costs = (runs ? run_costs : block_costs)(tile_start, rb_seg);
-    for (int i = 0; i <= kNarrowTiling; ++i) {
-        // the 32-bit mask kernel runs two tile workgroups per CU
-        const bool one_frame = i == 0 || i == kNarrowTiling;
-        std::vector<uint32_t> k = one_frame ? choose_tiles(costs, i == 0 ? n_cu : 2 * n_cu)
-                                            : std::vector<uint32_t>(sp->n_rb, 1u << (i - 1));
-        TilingHost h;
-        (runs ? make_run_tiling : make_tiling)(tile_start, seg_word, rb_seg, k, &h);
-        if (runs)
-            for (SpRound &r : h.rounds)
-                r.tcell = a->order.morton ? r.tword * 64u : a->order.word_cell[(uint64_t)r.tword * 64];
-        // the tile kernels address a task's entries (8 bytes each) and round
-        // records with 32-bit byte offsets
-        for (const SpTask &t : h.tasks)
-            LBL_REQUIRE((uint64_t)t.n_rounds * sizeof(SpRound) < (1ull << 32) &&
-                            (t.n_rounds == 0 || (uint64_t)h.rounds[t.round0 + t.n_rounds - 1].e_off + 64 < (1ull << 29)),
-                        "a tile task spans more entries than the tile kernels address");
-        lbl_status st = upload_tiling(h, &sp->tilings[i], &sp->round_bytes);
-        if (st != LBL_OK) return st;
-        CompactHost c;
-        if (make_compact(h, rows_host, tile_start, rb_seg, a->n_traj, &c)) {
-            st = upload_compact(c, &sp->tilings[i], &sp->round_bytes);
-            if (st != LBL_OK) return st;
-        }
-
-    }
-    {
-        lbl_status st = build_row_tiles(a, *sp, seg_start, seg_word, rb_seg, &sp->row_tiles);
-        if (st != LBL_OK) return st;
-        if (sp->row_tiles) {
-            sp->round_bytes += sp->row_tiles->bytes();
-            if (runs) {  // no kernel reads the words in this order then
-                (void)hipFree(sp->row);
-                (void)hipFree(sp->val);
-                sp->row = nullptr;
-                sp->val = nullptr;
-            }
-        }
-        // the direct-mask kernel's tiles: two workgroups per CU
-        DirectHost dh;
-        make_direct(seg_start, rb_seg, 2 * n_cu, &dh);
-        st = upload_direct(dh, seg_word, !sp->row_tiles, &sp->direct, &sp->round_bytes);
-        if (st != LBL_OK) return st;
-    }
+    size_t free_bytes = 0, total = 0;
+    LBL_HIP_TRY(hipMemGetInfo(&free_bytes, &total));
+    const lbl_status st = with_copies(copies_fit(nnz, free_bytes), [&](bool copies) {
+        return lay_out(a, sp.get(), seg_start, seg_word, rb_seg, copies);
+    });
+    if (st != LBL_OK) return st;
     LBL_HIP_TRY(hipDeviceSynchronize());
     a->sp = sp.release();
     return LBL_OK;

@@ -61,9 +61,31 @@ static void masks_from_frame()
         CHECK(tiles_pack(c.n_ent, c.n_seg, c.n_props, c.aligned) == c.pays);
 }
 
+// The copies of a layout's words: made first, dropped where they fail for want
+// of memory or offsets, kept out where memory is short.
+static void copies()
+{
+    CHECK(copies_fit(0, 0) && copies_fit(1000000, 1ull << 30) && !copies_fit(4000000, 1ull << 30));
+    CHECK(copies_fit(37000000, 280ull << 30) && !copies_fit(10000000000ull, 288ull << 30));
+    for (lbl_status first : {LBL_OK, LBL_ENOMEM, LBL_EINVAL, LBL_EDEVICE})
+        for (lbl_status second : {LBL_OK, LBL_ENOMEM}) {
+            std::vector<bool> made;
+            auto make = [&](bool c) {
+                made.push_back(c);
+                return c ? first : second;
+            };
+            const bool again = first == LBL_ENOMEM || first == LBL_EINVAL;
+            CHECK(with_copies(true, make) == (again ? second : first));
+            CHECK(made == (again ? std::vector<bool>{true, false} : std::vector<bool>{true}));
+            made.clear();
+            CHECK(with_copies(false, make) == second && made == std::vector<bool>{false});
+        }
+}
+
 int main()
 {
     plan_blocks();
+    copies();
     masks_from_frame();
     one_launch();
     if (fails) return 1;
