@@ -254,9 +254,9 @@ lbl_status plan_batch(const JobRef *jobs, size_t n_jobs, int device, BatchPlan *
             }
             p.lg_seg.push_back((uint32_t)p.segs.size());
             p.ow_off.push_back(p.ow_bytes);
-            // bitpacked plans: masks [w][G64][64 columns]; sparse plans:
-            // nibble tables [w][G64][256]
-            p.ow_bytes += up256((size_t)a->n_words * g.G64 * (p.sparse ? 256 : 64) * sizeof(uint64_t));
+            // bitpacked plans: masks [w][G64][64 columns]; sparse plans: nibble
+            // tables [w][G64][256], or cell masks [w][G64][64] for run layouts
+            p.ow_bytes += up256((size_t)a->n_words * g.G64 * (p.sparse ? a->sp->word_masks() : 64) * sizeof(uint64_t));
             p.pack_units += (uint64_t)a->n_words * g.G64;
             p.max_g64 = std::max(p.max_g64, g.G64);
             p.groups.push_back(g);

@@ -169,6 +169,8 @@ struct SparseLayout {
     std::unique_ptr<RowTiles> row_tiles;
     size_t round_bytes = 0;      // device bytes of all tilings' tables
     void drop_tiles();           // releases everything over the words
+    // masks a frame holds per word: its cells', or its nibble tables' entries
+    uint32_t word_masks() const { return ent ? 64 : 256; }
     ~SparseLayout();
 };
 
@@ -203,12 +205,16 @@ lbl_status sparse_part(const uint64_t *T, uint32_t row_stride, uint64_t n_rows, 
 lbl_status sparse_assemble(lbl_abs *a, std::vector<SparsePart> &parts);
 
 // Workspace bytes for one frame of n_lane_groups 64-column groups on tiling
-// t (nibble tables + per-tile partial labels); for one frame (the defaults),
-// the larger of the 64-bit and the 32-bit mask paths.
+// t (cell masks or nibble tables, and per-tile partial labels); for one frame
+// (the defaults), the larger of the 64-bit and the 32-bit mask paths.
 size_t swm_workspace_bytes(const lbl_abs *a, uint32_t n_lane_groups = 1, int t = 0);
 // Workspace bytes run_swm needs for one frame of n_props propositions (the
 // kernels that frame takes).
 size_t swm_frame_workspace_bytes(const lbl_abs *a, uint32_t n_props);
+// The need lbl_label_frame_noalloc states and holds its array against: that of
+// nibble tables, whatever the layout, so that a frame's acceptance does not
+// hang on how its T is stored.
+size_t swm_noalloc_bytes(const lbl_abs *a, uint32_t n_props);
 
 // Pack O, label through the tiled layout, write L (device pointers).
 // spans: record profiling events around the kernels (when profiling is on).

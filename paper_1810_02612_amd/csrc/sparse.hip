@@ -2496,9 +2496,11 @@ bool takes_direct(const SparseLayout &sp, uint32_t n_props, uint32_t *np)
            (size_t)sp.direct.max_part_segs * *np * sizeof(uint64_t) <= kDirectMaskBytes;
 }
 
-}  // namespace
+// Bytes of a frame's (or lane group's) per-word masks: 64 cells' for run
+// layouts, 256 table entries for nibble layouts.
+size_t word_mask_bytes(const lbl_abs *a, size_t mask) { return up256((size_t)a->n_words * a->sp->word_masks() * mask); }
 
-size_t swm_frame_workspace_bytes(const lbl_abs *a, uint32_t n_props)
+size_t frame_bytes(const lbl_abs *a, uint32_t n_props, uint32_t word_masks)
 {
     const SparseLayout &sp = *a->sp;
     uint32_t np = 0;
@@ -2506,11 +2508,17 @@ size_t swm_frame_workspace_bytes(const lbl_abs *a, uint32_t n_props)
     auto bytes = [&](int ti, size_t mask) {
         const SpTiling &tl = sp.tilings[ti];
         const size_t partials = tl.tile_slot ? (size_t)tl.n_slots : (size_t)tl.n_tiles * kRowBlock;
-        return up256((size_t)a->n_words * 256 * mask) + partials * mask;
+        return up256((size_t)a->n_words * word_masks * mask) + partials * mask;
     };
     if (n_props <= 32 && (int)sp.tilings.size() > kNarrowTiling) return bytes(kNarrowTiling, sizeof(uint32_t));
     return bytes(0, sizeof(uint64_t));
 }
+
+}  // namespace
+
+size_t swm_frame_workspace_bytes(const lbl_abs *a, uint32_t n_props) { return frame_bytes(a, n_props, a->sp->word_masks()); }
+
+size_t swm_noalloc_bytes(const lbl_abs *a, uint32_t n_props) { return frame_bytes(a, n_props, 256); }
 
 size_t swm_workspace_bytes(const lbl_abs *a, uint32_t n_lane_groups, int t)
 {
@@ -2518,7 +2526,7 @@ size_t swm_workspace_bytes(const lbl_abs *a, uint32_t n_lane_groups, int t)
         const SpTiling &tl = a->sp->tilings[ti];
         const size_t partials = tl.tile_slot && n_lane_groups == 1 ? (size_t)tl.n_slots
                                                                     : (size_t)n_lane_groups * tl.n_tiles * kRowBlock;
-        return up256((size_t)a->n_words * 256 * n_lane_groups * mask) + partials * mask;
+        return up256((size_t)a->n_words * a->sp->word_masks() * n_lane_groups * mask) + partials * mask;
     };
     size_t b = bytes(t, sizeof(uint64_t));
     if (t == 0 && n_lane_groups == 1 && (int)a->sp->tilings.size() > kNarrowTiling)
@@ -2535,7 +2543,7 @@ lbl_status run_swm_t(const lbl_abs *a, const SpTiling &tl, const uint8_t *O, uin
 {
     const SparseLayout &sp = *a->sp;
     M *Tg = static_cast<M *>(ws);
-    M *P = Tg + up256((size_t)a->n_words * 256 * sizeof(M)) / sizeof(M);
+    M *P = Tg + word_mask_bytes(a, sizeof(M)) / sizeof(M);
     auto span_begin = [&](hipStream_t st) { return spans ? lbl::span_begin(st) : nullptr; };
     auto span_end = [&](void *b, hipStream_t st, int kind) {
         if (spans) lbl::span_end(b, st, kind);
