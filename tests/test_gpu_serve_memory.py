@@ -1,4 +1,9 @@
-"""The server's accounting: what a request on a run layout is admitted against."""
+"""The server's accounting: what a request on a run layout is admitted against,
+batches that do not fit a slot in one piece, and the queue's bound while a
+batch is being planned."""
+import threading
+import time
+
 import numpy as np
 import pytest
 
@@ -51,3 +56,73 @@ def test_a_run_layout_needs_a_mask_per_cell(run_layout, props):
     mask = 4 if props <= 32 else 8
     need = high_water(run_layout, requests(run_layout, 1, props)[0], props)
     assert N * N * mask <= need < 2 * N * N * mask  # nibble tables would take four times as much
+
+
+def test_a_batch_that_does_not_fit_a_slot_is_split(run_layout):
+    reqs = requests(run_layout, 14, 64)
+    need = high_water(run_layout, reqs[0], 64)
+    s = lbl.serve_start(hbm_budget_bytes=4 * need, max_batch_frames=16, max_wait_us=0, n_streams=1)
+    try:
+        tickets = [lbl.serve_submit(s, run_layout[2], O, 64, L) for O, L, _ in reqs]
+        for t, (_, L, want) in zip(tickets, reqs):
+            assert lbl.serve_wait(s, t) == lbl.OK
+            assert np.array_equal(L.cpu().numpy(), want)
+        st = lbl.serve_stats(s)
+        assert st["completed"] == 14 and st["failed"] == 0
+        assert st["batches"] >= 4 and st["max_in_flight"] <= 5 and st["budget_high_water"] <= 4 * need, st
+    finally:
+        lbl.serve_stop(s)
+
+
+def test_the_queue_counts_requests_being_planned(run_layout):
+    """One batch in flight and a queue of 4: whatever is being planned counts
+    with the queue, so never more than 8 requests are unfinished."""
+    reqs = requests(run_layout, 6, 40)
+    s = lbl.serve_start(hbm_budget_bytes=1 << 30, max_batch_frames=4, max_wait_us=0, max_queue=4, n_streams=1)
+    accepted, busy, errors, most, stop = [0] * 6, [0] * 6, [], [0], threading.Event()
+
+    def client(i):
+        O, L, want = reqs[i]
+        for _ in range(150):
+            try:
+                t = lbl.serve_submit(s, run_layout[2], O, 40, L)
+            except lbl.LblError as e:
+                if e.status != lbl.EBUSY:
+                    errors.append(str(e))
+                busy[i] += 1
+                time.sleep(20e-6)
+                continue
+            accepted[i] += 1
+            tickets[i].append(t)
+            if len(tickets[i]) > 3 and lbl.serve_wait(s, tickets[i].pop(0)) != lbl.OK:
+                errors.append(lbl.last_error())
+
+    def watch():
+        while not stop.is_set():
+            st = lbl.serve_stats(s)
+            most[0] = max(most[0], st["submitted"] - st["completed"] - st["failed"])
+
+    tickets = [[] for _ in range(6)]
+    try:
+        w = threading.Thread(target=watch)
+        w.start()
+        th = [threading.Thread(target=client, args=(i,)) for i in range(6)]
+        for t in th:
+            t.start()
+        for t in th:
+            t.join()
+        for q in tickets:
+            for t in q:
+                assert lbl.serve_wait(s, t) == lbl.OK
+        stop.set()
+        w.join()
+        st = lbl.serve_stats(s)
+        print("queue of 4: accepted", sum(accepted), "busy", sum(busy), "most unfinished", most[0], flush=True)
+        assert not errors, errors[:3]
+        assert st["completed"] == sum(accepted) > 0 and st["rejected"] == sum(busy) > 0 and st["failed"] == 0, st
+        assert most[0] <= 8
+        for _, L, want in reqs:
+            assert np.array_equal(L.cpu().numpy(), want)
+    finally:
+        stop.set()
+        lbl.serve_stop(s)
