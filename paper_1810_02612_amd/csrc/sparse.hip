@@ -2078,8 +2078,8 @@ static lbl_status upload_compact(const CompactHost &c, SpTiling *t, size_t *byte
     return LBL_OK;
 }
 
-// upload false: only the split's sizes, which say whether a frame takes the
-// direct kernels (takes_direct).
+// upload false: only the split's sizes, by which lbl_label_frame_noalloc states
+// its need (swm_noalloc_bytes).
 static lbl_status upload_direct(const DirectHost &c, const std::vector<uint32_t> &seg_word, bool upload, DirectLayout *d,
                                 size_t *bytes)
 {
@@ -2486,6 +2486,8 @@ lbl_status build_sparse(lbl_abs *a)
 
 namespace {
 
+bool takes_row_tiles(const SparseLayout &sp, uint32_t n_props) { return n_props <= 4 && sp.row_tiles; }
+
 // Whether a frame of n_props propositions takes the direct-mask kernels
 // (the layout has their split and a part's segment masks fit their LDS);
 // *np is then the masks per word (1, 2 or 4).
@@ -2516,7 +2518,10 @@ size_t frame_bytes(const lbl_abs *a, uint32_t n_props, uint32_t word_masks)
 
 }  // namespace
 
-size_t swm_frame_workspace_bytes(const lbl_abs *a, uint32_t n_props) { return frame_bytes(a, n_props, a->sp->word_masks()); }
+size_t swm_frame_workspace_bytes(const lbl_abs *a, uint32_t n_props)
+{
+    return takes_row_tiles(*a->sp, n_props) ? 0 : frame_bytes(a, n_props, a->sp->word_masks());
+}
 
 size_t swm_noalloc_bytes(const lbl_abs *a, uint32_t n_props) { return frame_bytes(a, n_props, 256); }
 
@@ -2635,17 +2640,17 @@ lbl_status run_swm(const lbl_abs *a, const uint8_t *O, uint32_t n_props, void *w
 {
     LBL_REQUIRE(a->sp != nullptr, "the abstraction has no sparse layout");
     const SparseLayout &sp = *a->sp;
-    // frames of at most 4 propositions take the direct-mask kernel (which
-    // holds a part's segment masks in LDS), those of at most 32 the 32-bit
-    // mask kernels
+    // frames of at most 4 propositions take row tiles, or the direct-mask
+    // kernel (which holds a part's segment masks in LDS), those of at most 32
+    // the 32-bit mask kernels
+    if (takes_row_tiles(sp, n_props)) {
+        void *spn = spans ? span_begin(s) : nullptr;
+        const lbl_status st = run_row_tiles(a, *sp.row_tiles, O, n_props, L, s);
+        if (spans && st == LBL_OK) span_end(spn, s, 1);
+        return st;
+    }
     uint32_t np = 0;
     if (takes_direct(sp, n_props, &np)) {
-        if (sp.row_tiles) {
-            void *spn = spans ? span_begin(s) : nullptr;
-            const lbl_status st = run_row_tiles(a, *sp.row_tiles, O, n_props, L, s);
-            if (spans && st == LBL_OK) span_end(spn, s, 1);
-            return st;
-        }
         if (n_props == 1) return run_swm_direct<1>(a, O, n_props, ws, L, s, spans);
         if (n_props == 2) return run_swm_direct<2>(a, O, n_props, ws, L, s, spans);
         return run_swm_direct<4>(a, O, n_props, ws, L, s, spans);

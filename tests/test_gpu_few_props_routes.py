@@ -1,6 +1,7 @@
 """Frames of 1 to 4 propositions on the layouts that row tiles decline: by the
 direct-mask kernels, with frames and labels at odd offsets, and by the run
-kernels where a part's masks do not fit the direct kernel either.  The profile
+kernels where a part's masks do not fit the direct kernel either; and row tiles
+where only they hold a tile's masks.  The profile
 counts say which kernels ran (row tiles: no pack)."""
 import numpy as np
 import pytest
@@ -64,6 +65,28 @@ def test_run_kernels_below_four_propositions():
             L = torch.full((n_traj, P), 9, dtype=torch.uint8, device="cuda")
             print("run kernels", P, off, flush=True)
             assert profiled(h, ob[off:off + O.size], P, L) == (1, 1, 1)
+            assert np.array_equal(L.cpu().numpy(), oracle.label_csr(ptr, col, n * n, O, threads=8))
+    finally:
+        lbl.free_abstraction(h)
+
+
+def test_row_tiles_where_direct_masks_do_not_fit():
+    """3.2 million rows of 12 words that move slowly over 1024^2: 512 rows meet
+    some 140 words, a part of the direct split over 1,536."""
+    n, n_traj, per = 1024, 400 * 8192, 12
+    rng = np.random.default_rng(7)
+    ptr = np.arange(n_traj + 1, dtype=np.uint64) * per
+    w = (np.arange(n_traj) * 2000 // 8192)[:, None] % (n * n // 64 - per) + np.arange(per)
+    z = rng.integers(0, 64, w.shape)
+    col = ((w // (n // 8) * 8 + z // 8) * n + w % (n // 8) * 8 + z % 8).astype(np.uint32).reshape(-1)
+    h = lbl.load_abstraction(n, n, ptr, col, lbl.LOAD_SPARSE_ONLY)
+    try:
+        assert lbl.abstraction_info(h)["sparse_tiles_direct"] == -(-n_traj // 512)
+        for P in (1, 4):
+            O = (rng.random((n * n, P)) < 0.05).astype(np.uint8)
+            L = torch.full((n_traj, P), 9, dtype=torch.uint8, device="cuda")
+            print("row tiles beyond the direct split", P, flush=True)
+            assert profiled(h, torch.from_numpy(O).cuda(), P, L) == (0, 1, 0)
             assert np.array_equal(L.cpu().numpy(), oracle.label_csr(ptr, col, n * n, O, threads=8))
     finally:
         lbl.free_abstraction(h)
