@@ -34,7 +34,7 @@ __device__ __forceinline__ void emit_block(uint32_t *stage, uint32_t lane, uint3
     const uint32_t total = mis + n * np;  // bits, <= 15 + 4096
     const uint32_t n_units = (total + 15) >> 4;
     for (uint32_t w = lane; w < (total + 31) / 32; w += 64) stage[w] = 0;
-    __builtin_amdgcn_wave_barrier();
+    lds_in_order();
     if (lane < n) {
         const uint32_t o = mis + lane * np, sh = o & 31u;
         uint32_t *w = stage + (o >> 5);
@@ -47,10 +47,10 @@ __device__ __forceinline__ void emit_block(uint32_t *stage, uint32_t lane, uint3
         put(1, (uint32_t)(((uint64_t)hi << 32 | lo) >> (32 - sh)));
         put(2, sh ? hi >> (32 - sh) : 0u);
     }
-    __builtin_amdgcn_wave_barrier();
+    lds_in_order();
     // device memory (flat stores would also count on the LDS wait counter)
     __attribute__((address_space(1))) uint8_t *g = (__attribute__((address_space(1))) uint8_t *)(dst - mis);
-    const uint16_t *bits = reinterpret_cast<const uint16_t *>(stage);
+    const lds_u16 *bits = reinterpret_cast<const lds_u16 *>(stage);
     for (uint32_t u = lane; u < n_units; u += 64) {
         const uint32_t b16 = bits[u];
         const uint32_t lo = 16 * u, hi = lo + 16;
@@ -62,7 +62,7 @@ __device__ __forceinline__ void emit_block(uint32_t *stage, uint32_t lane, uint3
                 if (lo + b >= mis && lo + b < total) g[lo + b] = (uint8_t)((b16 >> b) & 1u);
         }
     }
-    __builtin_amdgcn_wave_barrier();  // the stage is reused by the next block
+    lds_in_order();  // the stage is reused by the next block
 }
 
 // emit_block for rows of 16 * upr bytes (upr = 1 .. 4) at a 16-byte aligned

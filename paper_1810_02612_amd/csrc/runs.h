@@ -14,6 +14,10 @@
 
 #include <cstdint>
 
+#ifdef __HIPCC__
+#include "tables.h"
+#endif
+
 namespace lbl {
 
 // A word's run tables: per tile row the 37 entries of its patterns, entry 0
@@ -114,7 +118,7 @@ __device__ __forceinline__ void build_runs(M m, M *t, uint32_t lane)
 #pragma unroll
     for (int j = 7; j >= 0; --j) {
         e[run_off(j + 1)] = v[j];
-        __builtin_amdgcn_wave_barrier();  // keeps the stores apart and in order
+        lds_in_order();  // keeps the stores apart as well
     }
 }
 

@@ -286,18 +286,16 @@ __device__ __forceinline__ uint64_t word_cell_mask(const uint8_t *__restrict__ O
             b = morton ? k : word_z(x, y);
         at[j] = 4u * b + part;  // 16-bit slot of the unit's bits in the stage
     }
-    // LDS accesses of one wavefront complete in issue order: the zeroing
-    // precedes the unit stores, which precede the reads (the barriers only
-    // keep the compiler from moving accesses across them)
+    // the zeroing precedes the unit stores, which precede the reads
     stage[lane] = 0;
-    __builtin_amdgcn_wave_barrier();
-    uint16_t *s16 = reinterpret_cast<uint16_t *>(stage);
+    lds_in_order();
+    lds_u16 *s16 = reinterpret_cast<lds_u16 *>(stage);
 #pragma unroll
     for (uint32_t j = 0; j < 4; ++j)
         if (j <= last) s16[at[j]] = (uint16_t)nz_bytes16(q[j]);
-    __builtin_amdgcn_wave_barrier();
+    lds_in_order();
     const uint64_t m = stage[lane];
-    __builtin_amdgcn_wave_barrier();
+    lds_in_order();
     return m;
 }
 
@@ -1313,15 +1311,12 @@ __device__ __forceinline__ void pack_words(const SegDesc &d, const uint64_t (&ce
     }
 #pragma unroll
     for (uint32_t w = 0; w < kPackWords; ++w) {
-        uint16_t *s16 = reinterpret_cast<uint16_t *>(stage + w * kPackStage);
+        lds_u16 *s16 = reinterpret_cast<lds_u16 *>(stage + w * kPackStage);
 #pragma unroll
         for (uint32_t k = 0; k < K; ++k)
             s16[l.lane + 64 * k] = (uint16_t)nz_bytes16(q[w][k].x, q[w][k].y, q[w][k].z, q[w][k].w);
     }
-    // LDS instructions of a wavefront complete in issue order; the barriers
-    // keep the compiler from moving the reads above the writes, or the next
-    // job's writes above these reads
-    __builtin_amdgcn_wave_barrier();
+    lds_in_order();
 #pragma unroll
     for (uint32_t w = 0; w < kPackWords; ++w) {
         const uint32_t o = 16 * l.run * run_units + ((mis[w] + (uint32_t)pack_run_offset(l.run, stride8)) & 15u) + l.pos * np;
@@ -1330,7 +1325,7 @@ __device__ __forceinline__ void pack_words(const SegDesc &d, const uint64_t (&ce
         const uint64_t v = (uint64_t)hi << 32 | lo;
         m[w] |= (np >= 64 ? v : v & ((1ull << np) - 1ull)) << d.bit;
     }
-    __builtin_amdgcn_wave_barrier();
+    lds_in_order();  // the next job writes the stage again
 }
 
 // One wavefront per pack item (pass, lane group, words [w0, w1)): for each

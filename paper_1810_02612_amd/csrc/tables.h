@@ -30,6 +30,17 @@ __device__ __forceinline__ uint32_t nz_bytes16(uint32_t x, uint32_t y, uint32_t 
 }
 __device__ __forceinline__ uint32_t nz_bytes16(const uint4 &q) { return nz_bytes16(q.x, q.y, q.z, q.w); }
 
+// Between LDS accesses of one wavefront, whose lanes read what others of it
+// wrote: the hardware completes them in issue order, and this keeps the compiler
+// from moving any across (the barrier alone is none for memory).
+__device__ __forceinline__ void lds_in_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+// Halves of LDS dwords that are also accessed whole.
+typedef uint16_t lds_u16 __attribute__((may_alias));
+
 // Loads from any byte address of device memory.
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
