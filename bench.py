@@ -122,8 +122,9 @@ def roofline(kernel: str, info: dict, n_traj: int, n_props: int, kernel_ms: floa
 
     bits    : dense bitpacked T (8 B per 64-cell word of every row) + packed
               frame masks (W x 64 x 8 B) + L (1 B per pair)          -> HBM
-    sparse  : sparse layout (10 B per (row, word) entry + the one-frame
-              tiling's task and round tables) + cell masks (W x 64 x 8 B)
+    sparse  : sparse layout (8 B per run entry, or 10 B per (row, word)
+              entry of nibble layouts, + the one-frame tiling's task and
+              round tables) + cell masks (W x 64 x 8 B)
               + label bits (8 B per row)                              -> HBM
               (frames of at most 32 propositions: their own tiling's
               tables, 4 B cell masks and 4 B of label bits per row;

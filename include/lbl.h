@@ -242,13 +242,12 @@ lbl_status lbl_label_frame_noalloc(lbl_abs_t a, const uint8_t *O, uint32_t n_pro
                                    void *hip_stream);
 
 /*
- * Label many frames, possibly against different abstractions, in one
- * persistent-kernel launch.  Each job is one frame as in lbl_label_frame
- * (device pointers; flags must be 0).  Jobs on the same abstraction share
- * each pass over T: their propositions are concatenated, up to
- * LBL_BATCH_MAX_PROPS per pass (more propositions on one abstraction take
- * further passes in the same launch).  Workgroups pull (abstraction, row
- * range) items from a queue, largest first.
+ * Label many frames, possibly against different abstractions, in one set of
+ * launches: packing, labeling, and label bytes.  Each job is one frame as in
+ * lbl_label_frame (device pointers; flags must be 0).  Jobs on the same
+ * abstraction share each pass over T: their propositions are concatenated, up
+ * to LBL_BATCH_MAX_PROPS per pass (more propositions on one abstraction take
+ * further passes in the same launches).
  *
  * A batch (its tables on the device and room for its packed masks and partial
  * labels) is laid out once for (hip_stream, jobs, launch choice) and kept for
@@ -265,16 +264,19 @@ lbl_status lbl_label_frame_noalloc(lbl_abs_t a, const uint8_t *O, uint32_t n_pro
  *
  * Jobs on one abstraction are placed into 64-column lane groups first-fit by
  * decreasing proposition count (a job never spans two lane groups).  With
- * the sparse layout on every abstraction, one wavefront per (word, lane
- * group) builds the nibble tables, one workgroup per CU pulls (tile, lane
- * group) items from per-XCD queues (items reading the same tables share an
- * XCD), and one wavefront per 64 rows of a lane group writes each job's
- * label bytes as one contiguous block.
+ * the sparse layout on every abstraction, wavefronts pack the words' cell
+ * masks or nibble tables, one workgroup takes each (tile, lane group) item,
+ * costliest first and items reading the same tables on one XCD (or, where
+ * lbl_tune_batch found it faster, one workgroup per CU pulls items from
+ * per-XCD queues), and one wavefront per 64 to 256 rows of a lane group writes
+ * each job's label bytes.  Without it one persistent kernel's workgroups pull
+ * (abstraction, row range) items, largest first.
  *
  * Errors: as lbl_label_frame for every job, plus LBL_EINVAL for n_jobs == 0,
- * nonzero flags, or a batch mixing an abstraction without the sparse layout
+ * nonzero flags, a batch mixing an abstraction without the sparse layout
  * (LBL_LOAD_NO_SPARSE) and one without the bitpacked T
- * (LBL_LOAD_SPARSE_ONLY): such a batch has no common kernel.
+ * (LBL_LOAD_SPARSE_ONLY): such a batch has no common kernel, or one recorded
+ * batch too many.
  */
 typedef struct {
     lbl_abs_t a;
@@ -364,8 +366,9 @@ lbl_status lbl_tune_describe(lbl_abs_t a, uint32_t n_props, char *buf, size_t bu
  * its own streams and a worker thread.  lbl_serve_submit enqueues one frame
  * (device pointers, as in lbl_label_frame) and returns a ticket; requests are
  * admitted onto the GPU as memory within hbm_budget_bytes (for the server's
- * internal per-request buffers) frees up, grouped per abstraction into
- * batches of at most max_batch_frames, and a batch is launched while earlier
+ * internal per-request buffers) frees up, in the order they came and in
+ * batches of at most max_batch_frames, whose requests on one abstraction share
+ * its passes, and a batch is launched while earlier
  * ones are still running (a batch of one frame on an abstraction with the
  * sparse layout runs the kernels lbl_label_frame's sparse path runs; the
  * labels are the same either way).  The library does not copy O or L: both must stay
@@ -479,7 +482,10 @@ lbl_status lbl_cell_position(const lbl_grid *grid, uint32_t cell, uint32_t *word
  *   n_sweeps             optional: relaxation sweeps up to and including
  *                        the first that brought no vertex nearer (at most
  *                        n_vertices * n_states + 1; a few more are enqueued
- *                        ahead and change nothing).
+ *                        ahead and change nothing).  A sweep may relax an
+ *                        edge more than once, as its vertices come nearer, so
+ *                        the count hangs on timing and may differ between
+ *                        equal calls; dist and pred do not.
  *
  * Synchronous: enqueued on hip_stream (0 = the null stream), returns when the
  * outputs are written; the host polls meanwhile.  Uses the stream's workspace

@@ -1,5 +1,5 @@
-// Batched labeling: many frames over several abstractions in one persistent
-// launch.  Used by lbl_label_batch (plans kept) and by the server.
+// Batched labeling: many frames over several abstractions in one set of
+// launches.  Used by lbl_label_batch (plans kept) and by the server.
 #pragma once
 
 #include "lbl_internal.h"
@@ -218,7 +218,8 @@ lbl_status bind_batch(const BatchPlan &plan, uint8_t *base, size_t capacity, Bat
                       std::vector<uint8_t> *host_image);
 size_t batch_table_bytes(const BatchPlan &plan);
 
-// Enqueue: counter reset, O packing for every job, persistent label kernel.
+// Enqueue: counter reset (queues and bitpacked plans), O packing for every job,
+// the label kernel, and on sparse plans the label bytes.
 lbl_status enqueue_batch(const BatchPlan &plan, const BatchBuffers &bufs, hipStream_t s);
 
 int device_cu_count();

@@ -1,15 +1,20 @@
-// Batched labeling in one persistent launch.
+// Batched labeling in one set of launches.
 //
 // Jobs on the same abstraction form a group: their propositions are laid
 // side by side in G64 lane groups of 64, so one pass over T labels all of
 // them (T is read once per batch, not once per frame).  The O packing of
-// every job is one kernel; the labeling is one persistent kernel whose
-// workgroups pull (group, row range) items from an atomic counter, largest
-// items first, so uneven abstractions share the GPU without a tail of idle
-// CUs.  lbl_label_batch keeps a batch's plan and device tables by (stream,
-// jobs, flags) and launches its kernels again when the batch comes again (a
-// captured graph of them took 25 us of host time to replay, the three launches
-// 8: 25k rows x 128^2, 4 frames, 39 us per call against 32).
+// every job is one kernel.  Sparse plans label with one workgroup per (tile,
+// lane group) item, costliest first (or persistent workgroups and per-XCD
+// queues, where tuned), and write the label bytes in a third kernel; bitpacked
+// plans with one persistent kernel whose workgroups pull (group, row range)
+// items from an atomic counter, largest first, so that uneven abstractions
+// share the GPU without a tail of idle CUs.
+//
+// lbl_label_batch keeps a batch's plan and device tables by (stream, jobs,
+// flags) and launches its kernels again when the batch comes again (a captured
+// graph of them took 25 us of host time to replay, the three launches 8: 25k
+// rows x 128^2, 4 frames, 39 us per call against 32; bitpacked batches, whose
+// kernel is longer, 1.00-1.04 times as fast).
 #include <algorithm>
 #include <cstring>
 #include <list>

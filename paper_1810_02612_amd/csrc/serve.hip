@@ -6,10 +6,10 @@
 // hbm_budget / n_streams bytes for the batch's tables and packed masks.
 // Whenever a slot is free and requests are pending, the worker forms a batch
 // from the front of the queue (at most max_batch_frames requests, as many as
-// fit the arena: admission by memory) and launches it with the same
-// persistent kernel as lbl_label_batch (a batch of one frame: the one-frame
-// kernels), while earlier batches are still running on the other slots.  Requests that arrive meanwhile join the next
-// batch.  While batches are in flight the worker polls their completion
+// fit the arena: admission by memory) and launches it with lbl_label_batch's
+// kernels (a batch of one frame: the one-frame kernels), while earlier batches
+// are still running on the other slots.  Requests that arrive meanwhile join
+// the next batch; the worker plans and enqueues with its lock released.  While batches are in flight the worker polls their completion
 // events every few microseconds (it sleeps on a condition variable only when
 // idle).  Latency is completion minus submission on the host's monotonic
 // clock.  A frame's columns never share lanes with another frame's, so its

@@ -41,7 +41,8 @@
 // few segments (tiles_pack) k_label_runs_frame forms the masks from O as well,
 // and there is no pack kernel; the smallest frames (one_launch_pays) take
 // k_label_runs_whole alone.
-// Frames of at most 4 propositions take two other kernels instead:
+// Frames of at most 4 propositions take row tiles (rowtiles.hip) where the layout
+// has them, else two other kernels:
 //   k_pack_masks   O -> NP proposition masks per used word (bit b = cell b);
 //                  the grid also zeroes L.
 //   k_label_direct one workgroup per tile of equal chunk count: a label bit
@@ -727,10 +728,11 @@ struct FrameCells {
 // at most two segments, and builds at most one segment's run tables.  Each
 // entry says itself which of the wavefront's two table slots it reads.
 //
-// Bound by the LDS: at 200k x 512^2 x 64 it is busy 35k of the 52k cycles a
-// CU runs (half of that for the table builds, eight 8-byte stores per lane
-// for each of 103k segments), the vector units 27k; loading the entries
-// alone, without lookups, takes 17 us of the 26, launch and write-back 6.
+// Bound by the LDS: at 200k x 512^2 x 64 it is active 36k of the 55k cycles a
+// CU is busy (half of that for the table builds, eight 8-byte stores per lane
+// for each of 103k segments; 27% of it bank conflicts), the vector units
+// 28.5k; loading the entries alone, without lookups, takes 17 us of the 26,
+// launch and write-back 6.
 // There: 45 vector and 14 LDS instructions per 64 entries where the nibble
 // kernel needs 51 and 19, 26.0 us against 28.6 (rocprofv3 medians), entries
 // 80 MB against 99; packing 5.2 us against 7.1, as it writes 512 bytes per
@@ -857,6 +859,19 @@ __device__ __forceinline__ void write_partials_compact(const void *lds, M *__res
     for (uint32_t k = threadIdx.x; k < n_slot; k += 64 * WAVES) __builtin_nontemporal_store(acc[rows[k]], dst + k);
 }
 
+// The tile's labels as its partials, compact or of every row.
+template <int WAVES, typename M>
+__device__ __forceinline__ void tile_partials(const void *lds, uint32_t tile, M *__restrict__ P,
+                                              const uint32_t *__restrict__ tile_slot, const uint16_t *__restrict__ slot_row)
+{
+    if (tile_slot) {
+        const uint32_t s0 = tile_slot[tile], s1 = tile_slot[tile + 1];
+        write_partials_compact<WAVES, M>(lds, P + s0, slot_row + s0, s1 - s0);
+    } else {
+        write_partials<WAVES, M>(lds, P + (uint64_t)tile * kRowBlock);
+    }
+}
+
 // One workgroup per tile of a single frame: workgroup b runs tile
 // block_tile[b], whose tasks tasks_launch holds at b * WAVES (no dependent
 // load before the first task).  Partials P[tile][kRowBlock].
@@ -871,25 +886,7 @@ k_label_tiles(const uint32_t *__restrict__ block_tile, const SpTask *__restrict_
     extern __shared__ uint64_t lds[];
     const uint32_t tile = block_tile[blockIdx.x];
     tile_accumulate<WAVES, M>(tasks_launch + (uint64_t)blockIdx.x * WAVES, rounds, sp_row, sp_val, Tg, 256, lds);
-    if (tile_slot) {
-        const uint32_t s0 = tile_slot[tile], s1 = tile_slot[tile + 1];
-        write_partials_compact<WAVES, M>(lds, P + s0, slot_row + s0, s1 - s0);
-    } else {
-        write_partials<WAVES, M>(lds, P + (uint64_t)tile * kRowBlock);
-    }
-}
-
-// The tile's labels as its partials, compact or of every row.
-template <int WAVES, typename M>
-__device__ __forceinline__ void tile_partials(const void *lds, uint32_t tile, M *__restrict__ P,
-                                              const uint32_t *__restrict__ tile_slot, const uint16_t *__restrict__ slot_row)
-{
-    if (tile_slot) {
-        const uint32_t s0 = tile_slot[tile], s1 = tile_slot[tile + 1];
-        write_partials_compact<WAVES, M>(lds, P + s0, slot_row + s0, s1 - s0);
-    } else {
-        write_partials<WAVES, M>(lds, P + (uint64_t)tile * kRowBlock);
-    }
+    tile_partials<WAVES, M>(lds, tile, P, tile_slot, slot_row);
 }
 
 // k_label_tiles for a layout in run entries (Tm: k_pack_cells' masks).
