@@ -2223,14 +2223,17 @@ bool one_launch_pays(uint64_t n_ent, uint64_t n_seg, uint32_t n_rb, uint32_t n_p
 // 16.0 (10k); 12,452 x 96 x 312 x 34 14.0, 11.9 (3k); 120,000 x 256^2 x 17 16.6, 22.4 (30k); 75,003 x 328^2 x 37 17.2,
 // 21.2 (50k).  A round that builds no tables loads the pieces of one cell all the
 // same, which costs where a 16-byte piece lies off dword alignment; with the pack
-// kernel and without, rounds x pieces in brackets: 27,710 x 64^2 x 31 12.5, 10.4
-// (5.7k); 34,551 x 64^2 x 22 13.5, 11.7 (7.8k); 70,632 x 64 x 96 x 30 12.5, 12.4 (11k);
-// 52,439 x 64^2 x 31 13.9, 14.7 (13k); 26,929 x 64^2 x 33 13.2, 12.9 (9.3k); 22,607 x
-// 64^2 x 42 14.4, 16.5 (9.7k); 49,860 x 72 x 64 x 59 13.1, 15.9 (19k).
+// kernel and without, such rounds (those beyond one a segment) x pieces in
+// brackets: 27,710 x 64^2 x 31 12.5, 10.4 (5.2k); 34,551 x 64^2 x 22 13.5, 11.7
+// (7.1k); 70,632 x 64 x 96 x 30 12.5, 12.4 (9.8k); 52,439 x 64^2 x 31 13.9, 14.7
+// (13k); 12,974 x 96 x 320 x 38 15.2, 14.4 (6.7k); 26,929 x 64^2 x 33 13.2, 12.9
+// (8.6k); 22,607 x 64^2 x 42 14.4, 16.5 (9.1k); 43,175 x 64^2 x 35 13.9, 12.5 (9.9k);
+// 59,460 x 64 x 96 x 47 14.0, 12.2 (11k); 49,860 x 72 x 64 x 59 13.1, 15.9 (17k).
 bool tiles_pack(uint64_t n_ent, uint64_t n_seg, uint32_t n_props, bool aligned)
 {
-    const uint64_t pieces = n_props < 16 ? 2 : (n_props + 15) / 16;
-    if (!aligned && n_props >= 16 && n_ent / 64 * pieces > (n_props <= 32 ? 12500 : 9500)) return false;
+    const uint64_t pieces = n_props < 16 ? 2 : (n_props + 15) / 16, rounds = n_ent / 64;
+    const uint64_t idle = rounds > n_seg ? rounds - n_seg : 0;
+    if (!aligned && n_props >= 16 && idle * pieces > 11000) return false;
     return n_seg <= (1ull << 32) && n_seg * pieces * (aligned ? 1 : 16) <= 50000;
 }
 

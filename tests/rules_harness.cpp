@@ -56,7 +56,7 @@ static void masks_from_frame()
         bool aligned, pays;
     };
     for (const Case &c : {Case{800000, 7168, 32, true, true}, Case{2300000, 30000, 64, true, false}, Case{183747, 256, 31, false, true},
-                          Case{206665, 192, 42, false, false}, Case{429803, 448, 31, false, false}, Case{438214, 448, 17, false, false},
+                          Case{276204, 768, 47, false, true}, Case{204296, 960, 38, false, true}, Case{367339, 864, 30, false, true}, Case{429803, 448, 31, false, false}, Case{438214, 448, 17, false, false},
                           Case{438214, 448, 16, true, true}, Case{1459632, 1408, 13, false, true}, Case{855870, 1224, 47, false, false}})
         CHECK(tiles_pack(c.n_ent, c.n_seg, c.n_props, c.aligned) == c.pays);
 }
